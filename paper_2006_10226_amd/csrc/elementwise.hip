@@ -12,6 +12,7 @@
 #include "qnn_internal.h"
 
 #include <algorithm>
+#include <numeric>
 
 namespace qnn {
 
@@ -214,6 +215,114 @@ __global__ void __launch_bounds__(256) requantize_kernel(ReqArgs a)
     }
 }
 
+// The form for 8-bit outputs with every shift in [33, 53] (a.fast) on
+// aligned buffers; bound by HBM traffic.  A thread takes groups of E
+// consecutive elements, E so that neighbouring lanes load neighbouring 16
+// bytes, at a grid stride that is a multiple of the channel count (the host
+// sees to it): its E channels stay the same, so their records are read once
+// and kept in registers, and the rounding is a 32-bit one.  An int32 ->
+// uint8 pass per channel over 32 x 56 x 56 x 256 (128 MB) took 66 us through
+// the general kernel (16 bytes of table per element, 64-bit products, lanes
+// 64 bytes apart) and takes 23.5 us (5.5 TB/s).
+template <int XDT, int YDT, bool PERCH>
+__global__ void __launch_bounds__(256) requantize_fast_kernel(ReqArgs a)
+{
+    constexpr int E = XDT == 2 ? 4 : 16;
+    constexpr int U = XDT == 2 ? 4 : 2;    // groups in flight
+    constexpr int NR = PERCH ? E : 1;
+    constexpr int OFF = YDT == 1 ? 128 : 0;
+    const long long groups = a.count / E;
+    const long long stride = (long long)gridDim.x * 256;
+    const long long g0 = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (g0 == 0)   // the elements after the last whole group
+        for (long long i = groups * E; i < a.count; ++i)
+            st<YDT>(a.y, i, req_one(a, ld<XDT>(a.x, i), a.tab ? (int)(i % a.channels) : 0));
+    if (g0 >= groups)
+        return;
+    int mult[NR], sh[NR], rnd[NR], zi[NR], zo[NR];
+    int c = PERCH ? (int)(g0 * E % a.channels) : 0;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        int4 t = int4{a.mult, a.shift, a.zp_in, a.zp_out};
+        if constexpr (PERCH)
+            t = *(const int4 *)(a.tab + 4 * c);
+        mult[k] = t.x;
+        sh[k] = t.y - 32;
+        zi[k] = t.z;
+        zo[k] = t.w + OFF;
+        rnd[k] = (1 << (sh[k] - 1)) + (zo[k] << sh[k]);
+        if (++c == a.channels)
+            c = 0;
+    }
+    const int lo = a.lo + OFF, hi = a.hi + OFF;
+    auto one = [&](int q, int k, int mode) {
+        const int i = PERCH ? k : 0;
+        const int v = XDT == 2 ? q : q - zi[i];   // int32 inputs have zero point 0
+        return (uint32_t)clamp_i32(rounding_mul_shift32(v, mult[i], sh[i], rnd[i], zo[i], mode), lo, hi);
+    };
+    for (long long g = g0; g < groups; g += U * stride) {
+        v4i in[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (g + u * stride < groups)
+                in[u] = __builtin_nontemporal_load((const v4i *)a.x + (g + u * stride));
+        auto put = [&](int mode) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (g + u * stride >= groups)
+                    break;
+                uint32_t w[E / 4];
+#pragma unroll
+                for (int k = 0; k < E / 4; ++k) {
+                    w[k] = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        int q;
+                        if constexpr (XDT == 2)
+                            q = in[u][e];
+                        else
+                            q = XDT == 1 ? (int)(int8_t)((uint32_t)in[u][k] >> (8 * e))
+                                         : (int)(((uint32_t)in[u][k] >> (8 * e)) & 0xffu);
+                        w[k] |= one(q, 4 * k + e, mode) << (8 * e);
+                    }
+                    if constexpr (YDT == 1)
+                        w[k] ^= 0x80808080u;
+                }
+                if constexpr (E == 4)
+                    __builtin_nontemporal_store(w[0], (uint32_t *)a.y + (g + u * stride));
+                else
+                    __builtin_nontemporal_store(v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]},
+                                                (v4i *)a.y + (g + u * stride));
+            }
+        };
+        if (a.rounding == 0)
+            put(0);
+        else if (a.rounding == 1)
+            put(1);
+        else
+            put(2);
+    }
+}
+
+// Workgroups of the fast form, 0 where it does not apply: at most eight per
+// CU, and (unless every thread has one group only) a multiple that makes the
+// grid stride a multiple of the channel count.
+static int req_fast_grid(const ReqArgs &a, int xdt, bool aligned)
+{
+    if (!a.fast || !aligned)
+        return 0;
+    const int E = xdt == 2 ? 4 : 16;
+    const long long need = (a.count / E + 255) / 256;
+    const int cap = 2048;
+    if (need <= cap)
+        return need > 0 ? (int)need : 1;
+    if (!a.tab)
+        return cap;
+    const int period = a.channels / std::gcd(a.channels, E);   // groups until the channels repeat
+    const int q = period / std::gcd(period, 256);
+    return q <= cap ? cap / q * q : 0;
+}
+
 // With a.tab_ok each workgroup first tabulates the two terms for every
 // operand byte in LDS (256 threads, one byte each), and an element is then
 // clamp(tab[a] + tab[256 + b]).
@@ -265,6 +374,13 @@ static dim3 ew_grid(long long count)
 template <int XDT, int YDT>
 static void req_launch(const ReqArgs &a, bool vec, hipStream_t s)
 {
+    if constexpr (YDT != 2) {
+        if (const int grid = req_fast_grid(a, XDT, vec)) {
+            if (a.tab) launch_main((requantize_fast_kernel<XDT, YDT, true>), dim3(grid), dim3(256), 0, s, a);
+            else launch_main((requantize_fast_kernel<XDT, YDT, false>), dim3(grid), dim3(256), 0, s, a);
+            return;
+        }
+    }
     if (vec) launch_main((requantize_kernel<XDT, YDT, true>), ew_grid(a.count), dim3(256), 0, s, a);
     else launch_main((requantize_kernel<XDT, YDT, false>), ew_grid(a.count), dim3(256), 0, s, a);
 }

@@ -1558,6 +1558,9 @@ qnn_status make_req_plan(qnn_dtype xt, int64_t count, int32_t channels, qnn_qpar
     a.channels = channels;
     a.mult = tab[0]; a.shift = tab[1]; a.zp_in = tab[2]; a.zp_out = tab[3];
     a.lo = lo; a.hi = hi; a.rounding = rnd;
+    a.fast = yt != QNN_INT32;
+    for (int c = 0; c < nc; ++c)
+        a.fast = a.fast && tab[4 * c + 1] >= 33 && tab[4 * c + 1] <= 53;
     a.tab = nullptr;
     if (perch) {
         if (!upload) {

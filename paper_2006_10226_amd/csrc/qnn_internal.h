@@ -83,6 +83,33 @@ __device__ __forceinline__ long long rounding_mul_shift(int v, int mult, int shi
     return (p + (1LL << (shift - 1)) - (mode == 1 && p < 0 ? 1 : 0)) >> shift;
 }
 
+// The same value in 32-bit operations, less the final division's rounding
+// constant: for 33 <= shift <= 53, with hi and lo the words of p = v * mult
+// (|hi| <= 2^30),
+//   HALF_UP    floor((p + 2^(shift-1)) / 2^shift) = (hi + 2^(shift-33)) >> (shift-32):
+//              the low word only adds a fraction below 1 before the division;
+//   HALF_AWAY  p - 1 for negative p: the same with hi - 1 where v < 0 and
+//              lo == 0 (then the borrow reaches hi; elsewhere it stays in lo,
+//              whose value does not matter);
+//   TWO_STAGE  x1 = floor((p + 2^30) / 2^31) from the two words, then
+//              (x1 + 2^(shift-32) - (x1 < 0)) >> (shift-31), the sum held at
+//              INT32_MAX where it would pass it (the quotient is then at
+//              least 511, beyond every clamp of an 8-bit output).
+// Returns the quotient plus zp; sh = shift - 32, rnd = 2^(sh-1) + zp * 2^sh
+// with 0 <= zp <= 255 (HALF_UP and HALF_AWAY; exact in 32 bits).
+__device__ __forceinline__ int rounding_mul_shift32(int v, int mult, int sh, int rnd, int zp, int mode)
+{
+    const int hi = __mulhi(v, mult);
+    if (mode == 0)
+        return (hi + rnd) >> sh;
+    const uint32_t lo = (uint32_t)v * (uint32_t)mult;
+    if (mode == 1)
+        return (hi - (v < 0 && lo == 0 ? 1 : 0) + rnd) >> sh;
+    const int x1 = (int)(((uint32_t)hi << 1) + ((lo + 0x40000000u) >> 31) + (lo >= 0xc0000000u ? 2u : 0u));
+    const int half = 1 << sh;
+    return ((min(x1, INT32_MAX - half) + half - (x1 < 0 ? 1 : 0)) >> (sh + 1)) + zp;
+}
+
 // min(max(t, lo), hi) for lo <= hi (the host rejects empty clamps) in one
 // VALU operation; the compiler emits a max and a min for runtime bounds.
 __device__ __forceinline__ int clamp_i32(int t, int lo, int hi)
@@ -263,6 +290,7 @@ struct ReqArgs {
     int32_t channels;
     int32_t mult, shift, zp_in, zp_out;   // per-tensor values when tab == nullptr
     int32_t lo, hi, rounding;
+    int32_t fast;           // 8-bit output and every shift in [33, 53]: rounding_mul_shift32
 };
 
 
