@@ -274,6 +274,8 @@ __device__ __forceinline__ void add_bconst(v4i (&acc)[TC / WC / 16][TP / WP / 16
 #pragma unroll
             for (int j = 0; j < FP; ++j)
                 acc[i][j] += b;
+            if constexpr (FC * FP > 16)
+                lds_settled(acc[i]);   // these sums before the next records are read
         }
     }
 }
@@ -289,7 +291,10 @@ __device__ __forceinline__ void add_bconst(v4i (&acc)[TC / WC / 16][TP / WP / 16
 // records (channels c0 .. c0 + TC - 1) in LDS, and the accumulators
 // already hold bconst (see add_bconst).  FUSE: the staged copy-out applies the residual add (the
 // host launches these instantiations only with a.res set and a.staged).
-template <int TC, int TP, int WC, int WP, int STAGE_BYTES, bool FUSE = false>
+// PLAIN: no padding correction and no term 3 (the host launches these
+// instantiations only without either; the largest wave tiles have no
+// registers for them).
+template <int TC, int TP, int WC, int WP, int STAGE_BYTES, bool FUSE = false, bool PLAIN = false>
 __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC / 16][TP / WP / 16], int8_t *stage,
                                            int c0, int p0, const ChanRec *recs)
 {
@@ -315,7 +320,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC
         }
     }
 
-    if (a.pcorr) {
+    if (!PLAIN && a.pcorr) {
         // taps outside the image were gathered as x = 0; the padding value
         // is zp_x, so add zp_x * (weights of those taps), per border class
 #pragma unroll
@@ -331,7 +336,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC
             }
         }
     }
-    if (a.asum) {
+    if (!PLAIN && a.asum) {
         // term 3 of Eq. (3): - zp_w[k] * (window sum of x~' at pixel m)
 #pragma unroll
         for (int i = 0; i < FC; ++i) {

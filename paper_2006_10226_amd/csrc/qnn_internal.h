@@ -230,6 +230,15 @@ struct ConvArgs {
     // padded image (H, W padded, pads 0), R counts filter row pairs, S is 1,
     // and row_bytes is the padded image's row stride
     int32_t rowpack, row_bytes;
+    // short-loop kernel (conv_flow_kernel.h): its packed weights and their row
+    // stride and reduction length (wp's own, or with every tap padded to whole
+    // 16-byte chunks), 1x1 filter with every tap inside the image (linear),
+    // 16-byte chunks per tap, magic divisors by that, by S and by tiles_c,
+    // pixel tiles whose channel tiles are interleaved
+    const int8_t *fw;
+    int32_t fJpad, fJ;
+    int32_t linear, Cq, gp;
+    uint32_t mCq, sCq, mS, sS, mTC, sTC;
     // split reduction of the LDS-direct ring kernel: each tile's K-steps in
     // ksplit parts run by separate workgroups; part[] holds their int32
     // partial sums (ntiles * ksplit * TC * TP), cnt[] one arrival counter per
@@ -368,6 +377,56 @@ enum DmaTile {
     DMA_128x128_K2 = 28,
     DMA_COUNT
 };
+// Tile configurations of the short-loop kernel (conv_flow_kernel.h).
+enum FlowTile {
+    FLOW_64x64 = 0,
+    FLOW_128x64 = 1,
+    FLOW_64x128 = 2,
+    FLOW_128x128 = 3,
+    FLOW_256x128 = 4,     // 4x2 waves of 64x64 (512 threads)
+    FLOW_128x256 = 5,     // 2x4 waves of 64x64 (512 threads)
+    FLOW_256x256 = 6,     // 2x4 waves of 128x64 (512 threads)
+    // two groups of 2x2 waves taking alternate K-steps (512 threads)
+    FLOW_64x64_K2 = 7,
+    FLOW_128x64_K2 = 8,
+    FLOW_128x128_K2 = 9,
+    // short reductions, every stage in flight at once
+    FLOW_64x64_R1 = 10,
+    FLOW_64x128_R1 = 11,
+    FLOW_128x64_R1 = 12,
+    FLOW_64x64_R2 = 13,
+    FLOW_64x128_R2 = 14,
+    FLOW_128x64_R2 = 15,
+    FLOW_64x64_R4 = 16,
+    FLOW_64x128_R4 = 17,
+    FLOW_128x128_R4 = 18,
+    FLOW_COUNT
+};
+TileShape flow_tile_shape(int tile);
+int flow_threads(int tile);
+int flow_stages(int tile);
+bool flow_short(int tile);
+int flow_groups(int tile);
+int flow_wave_tile(int tile);   // channels x pixels of one wave
+size_t flow_lds_bytes(int tile, int nk, bool linear);   // LDS of a launch (fused-add tables included)
+hipError_t launch_conv_flow(const ConvArgs &a, int tile, hipStream_t st);
+// Kernel for few output pixels (conv_small.hip): channels x pixels per
+// workgroup, the reduction split over its eight waves.
+enum SmallTile {
+    SMALL_16x16 = 0,
+    SMALL_32x16 = 1,
+    SMALL_64x16 = 2,
+    SMALL_16x32 = 3,
+    SMALL_32x32 = 4,
+    SMALL_32x64 = 5,
+    SMALL_COUNT
+};
+TileShape small_tile_shape(int tile);
+size_t small_lds_bytes(int tile, int nk, bool linear);
+hipError_t launch_conv_small(const ConvArgs &a, int tile, hipStream_t st);
+hipError_t launch_tap_pack(const int8_t *w, int K, int RS, int C, int C16, int Kpad, int Jpad, int8_t *out,
+                           hipStream_t st);
+
 TileShape dma_tile_shape(int tile);
 int dma_threads(int tile);
 bool dma_splits(int tile);   // the configuration has a split-reduction form
