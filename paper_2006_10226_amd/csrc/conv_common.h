@@ -63,6 +63,54 @@ __device__ __forceinline__ uint32_t requant4(const ConvArgs &a, v4i acc, const v
     return packed;
 }
 
+// The same from records rec[e] that are KRecs (a.krec) or, for every other
+// plan, ChanRecs whose bconst is still to be added. With a KRec an output is
+// one 64-bit multiply-add, whose high word is the value that requant4 shifts,
+// and a shift, and where the clamp is the byte's own range four of them are
+// clamped and packed by five instructions: 13 for four outputs, with bconst,
+// where add_bconst and requant4 take 24. Every vector instruction used here
+// issues at one wave per four cycles (measured), so instructions are the cost:
+// 1x1 16 -> 96
+// at 112x112 batch 64 41.3 -> 36.1 us, 64 -> 256 at 56x56 batch 32 with a fused
+// add 20.8 -> 18.6 us, two dense layers of 4000 tokens 43 -> 37.5 us, the
+// ResNet-50 body at batch 32 712 -> 688 us.
+enum class Req { CHAN, SAT, CLAMP };   // ChanRec; KRec, full byte range; KRec, any clamp
+
+template <Req FORM>
+__device__ __forceinline__ uint32_t requant4_rec(const ConvArgs &a, v4i acc, const v4i (&rec)[4])
+{
+    uint32_t packed = 0;
+    if constexpr (FORM == Req::CHAN) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int v = (int)((uint32_t)acc[e] + (uint32_t)rec[e].y);   // wraps exactly when the sum fits
+            long long o = rounding_mul_shift(v, rec[e].x, rec[e].w, a.rounding) + a.zp_y;
+            o = o < a.lo ? a.lo : (o > a.hi ? a.hi : o);
+            packed |= ((uint32_t)o & 0xffu) << (8 * e);
+        }
+        return packed;
+    } else {
+        int t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const long long k = (long long)((uint64_t)(uint32_t)rec[e].x | (uint64_t)(uint32_t)rec[e].y << 32);
+            t[e] = (int)(((long long)acc[e] * rec[e].z + k) >> 32) >> (rec[e].w & 31);
+        }
+        if constexpr (FORM == Req::SAT) {
+            uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_i16(t[0], t[1]));
+            uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_i16(t[2], t[3]));
+            asm("v_sat_pk_u8_i16 %0, %1" : "=v"(lo) : "v"(lo));
+            asm("v_sat_pk_u8_i16 %0, %1" : "=v"(hi) : "v"(hi));
+            packed = lo | hi << 16;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                packed |= (uint32_t)clamp_i32(t[e], a.lo_off, a.hi_off) << (8 * e);
+        }
+        return packed ^ a.out_xor;
+    }
+}
+
 // Residual qnn.add fused into the epilogue.  The staged copy-out hands
 // thread tid the 16-byte chunks idx = it * NT + tid (it < ITERS) of the
 // tile: pixel row idx / CH, channels 16 * (idx % CH) on; the residual
@@ -143,6 +191,33 @@ __device__ __forceinline__ v4i residual_add16_tab(const ConvArgs &a, v4i v, v4i 
     return o;
 }
 
+// The add with both terms in f32 (AddArgs::flt): nine instructions per
+// element and no LDS. The tables' two reads at random addresses cost an LDS
+// about eight cycles each per wave, which every wave of the CU shares: fused
+// 1x1 64 -> 256 at 56x56 batch 32 22.1 us with tables, 20.8 us
+// so.
+__device__ __forceinline__ uint32_t residual_add4_f32(const ConvArgs &a, uint32_t v, uint32_t r)
+{
+    const uint32_t x = v ^ a.fadd.uxa, y = r ^ a.fadd.uxb;
+    uint32_t o = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float ta = __builtin_rintf(__builtin_fmaf((float)((x >> (8 * e)) & 0xffu), a.fadd.fma_a, a.fadd.fca));
+        const float tb = __builtin_rintf(__builtin_fmaf((float)((y >> (8 * e)) & 0xffu), a.fadd.fma_b, a.fadd.fcb));
+        o = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(ta + tb, a.fadd.flo, a.fadd.fhi), (uint32_t)e, o);
+    }
+    return o ^ a.fadd.uy;
+}
+
+__device__ __forceinline__ v4i residual_add16_f32(const ConvArgs &a, v4i v, v4i r)
+{
+    v4i o;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        o[w] = (int)residual_add4_f32(a, (uint32_t)v[w], (uint32_t)r[w]);
+    return o;
+}
+
 // LDS home of the term tables in the fused instantiations.
 template <bool FUSE>
 __device__ __forceinline__ lds_i32 *fuse_tables()
@@ -158,7 +233,8 @@ __device__ __forceinline__ lds_i32 *fuse_tables()
 // Copy-out of a staged tile (TP pixel rows of SP bytes in LDS, the tile's
 // first min(TC, kmax) channels valid) with the residual add applied, the
 // residual chunks prefetched in r (byte loads here where they were not);
-// tab: the term tables in LDS, or nullptr for the add's own arithmetic.
+// the f32 form where the plan has one, else tab: the term tables in LDS, or
+// nullptr for the add's own arithmetic.
 template <int TC, int TP, int NT, int SP>
 __device__ __forceinline__ void copy_out_residual(const ConvArgs &a, const int8_t *stage, int c0, int p0, int kmax,
                                                   const v4i (&r)[(TP * (TC / 16) + NT - 1) / NT],
@@ -183,7 +259,9 @@ __device__ __forceinline__ void copy_out_residual(const ConvArgs &a, const int8_
                 rv = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
             }
             const v4i sv = *(const v4i *)(stage + pl * SP + qc * 16);
-            const v4i v = tab ? residual_add16_tab(a, sv, rv, tab) : residual_add16(a, sv, rv);
+            const v4i v = a.fadd.flt ? residual_add16_f32(a, sv, rv)
+                          : tab      ? residual_add16_tab(a, sv, rv, tab)
+                                     : residual_add16(a, sv, rv);
             uint8_t *dst = (uint8_t *)a.y + (size_t)m * a.y_ldc + a.y_coff + c0 + qc * 16;
             if (n == 16) {
                 __builtin_nontemporal_store(v, (v4i *)dst);
@@ -294,7 +372,9 @@ __device__ __forceinline__ void add_bconst(v4i (&acc)[TC / WC / 16][TP / WP / 16
 // PLAIN: no padding correction and no term 3 (the host launches these
 // instantiations only without either; the largest wave tiles have no
 // registers for them).
-template <int TC, int TP, int WC, int WP, int STAGE_BYTES, bool FUSE = false, bool PLAIN = false>
+// KREC: recs holds the records of requant4_rec, and the accumulators don't
+// hold bconst.
+template <int TC, int TP, int WC, int WP, int STAGE_BYTES, bool FUSE = false, bool PLAIN = false, bool KREC = false>
 __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC / 16][TP / WP / 16], int8_t *stage,
                                            int c0, int p0, const ChanRec *recs)
 {
@@ -313,7 +393,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC
     if constexpr (FUSE) {
         static_assert(512 % NT == 0, "the term tables split evenly over the threads");
         residual_prefetch<TC, TP, NT>(a, c0, p0, rres);
-        if (a.fadd.tab) {
+        if (a.fadd.tab && !a.fadd.flt) {
 #pragma unroll
             for (int i = 0; i < 512 / NT; ++i)
                 tabv[i] = a.fadd.tab[i * NT + tid];
@@ -352,24 +432,42 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC
     if (a.staged) {
         constexpr int SP = (TP * (TC + 16) <= STAGE_BYTES) ? TC + 16 : TC;
         static_assert(TP * SP <= STAGE_BYTES, "output staging must fit the LDS buffers");
+        auto requantize = [&](auto form) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < FC; ++i) {
-            const int cl = wc * WTC + i * 16 + lchk * 4;
-            v4i rec[4];
+            for (int i = 0; i < FC; ++i) {
+                if (c0 + wc * WTC + i * 16 >= a.K)
+                    break;   // whole blocks past the last channel are not copied out
+                const int cl = wc * WTC + i * 16 + lchk * 4;
+                v4i rec[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-            {
-                rec[e] = lds_rec(recs + cl + e);
-                rec[e].y = 0;
+                for (int e = 0; e < 4; ++e) {
+                    rec[e] = lds_rec(recs + cl + e);
+                    if constexpr (!KREC)
+                        rec[e].y = 0;
+                }
+#pragma unroll
+                for (int j = 0; j < FP; ++j) {
+                    const int pl = wpos * WTP + j * 16 + lrow;
+                    uint32_t *dst = (uint32_t *)(stage + pl * SP + cl);
+                    if constexpr (KREC)
+                        *dst = requant4_rec<decltype(form)::value>(a, acc[i][j], rec);
+                    else
+                        *dst = requant4(a, acc[i][j], rec);
+                }
             }
-#pragma unroll
-            for (int j = 0; j < FP; ++j) {
-                const int pl = wpos * WTP + j * 16 + lrow;
-                *(uint32_t *)(stage + pl * SP + cl) = requant4(a, acc[i][j], rec);
-            }
+        };
+        if constexpr (!KREC) {
+            requantize(std::integral_constant<Req, Req::CHAN>{});
+        } else if (a.krec) {
+            if (a.sat_pack)
+                requantize(std::integral_constant<Req, Req::SAT>{});
+            else
+                requantize(std::integral_constant<Req, Req::CLAMP>{});
+        } else {
+            requantize(std::integral_constant<Req, Req::CHAN>{});
         }
         if constexpr (FUSE) {
-            if (a.fadd.tab) {
+            if (a.fadd.tab && !a.fadd.flt) {
 #pragma unroll
                 for (int i = 0; i < 512 / NT; ++i)
                     fuse_tables<FUSE>()[i * NT + tid] = tabv[i];
@@ -411,10 +509,10 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC
         const bool full = a.vec_store && ch + 3 < a.K;
         v4i rec[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-        {
+        for (int e = 0; e < 4; ++e) {
             rec[e] = lds_rec(recs + (ch - c0) + e);
-            rec[e].y = 0;
+            if constexpr (!KREC)
+                rec[e].y = 0;
         }
 #pragma unroll
         for (int j = 0; j < FP; ++j) {
@@ -436,7 +534,12 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, v4i (&acc)[TC / WC
                 }
                 continue;
             }
-            const uint32_t packed = requant4(a, acc[i][j], rec);
+            uint32_t packed;
+            if constexpr (KREC)
+                packed = a.krec ? requant4_rec<Req::CLAMP>(a, acc[i][j], rec)
+                                : requant4_rec<Req::CHAN>(a, acc[i][j], rec);
+            else
+                packed = requant4(a, acc[i][j], rec);
             uint8_t *yp = (uint8_t *)a.y + off;
             if (full) {
                 __builtin_nontemporal_store(packed, (uint32_t *)yp);

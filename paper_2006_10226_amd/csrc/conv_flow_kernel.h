@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
         // the tile's channel records, a kilobyte per load; older than this
         // wave's stage loads, so every stage wait covers them
         const __amdgpu_buffer_rsrc_t rc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)a.chan, (short)0, a.Kpad * (int)sizeof(ChanRec), kBufFlags);
+            __builtin_amdgcn_make_buffer_rsrc(a.krec ? (void *)a.krec : (void *)a.chan, (short)0, a.Kpad * (int)sizeof(ChanRec), kBufFlags);
 #pragma unroll
         for (int q = 0; q < TC / 64; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (__attribute__((address_space(3))) void *)(recs + q * 64), 16,
@@ -370,8 +370,6 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
             constexpr int k = decltype(S)::value;
             if constexpr (k < NS) {
                 stage_barrier<LPS *(NS - 1 - k)>();
-                if constexpr (k == 0)
-                    add_bconst<TC, TP, WC, WP, true>(acc, recs);   // the records landed with stage 0
                 if (k < nk) {
                     read_frags(std::integral_constant<int, k>{}, fa[0], fb[0]);
                     lds_wait<0>();
@@ -400,8 +398,6 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
             issue(s);
         }
         stage_barrier<LPS *(NSG - 2)>();
-        if (!BIG && grp == 0)
-            add_bconst<TC, TP, WC, WP, true>(acc, recs);   // the records landed with stage 0
         read_frags(std::integral_constant<int, 0>{}, fa[0], fb[0]);
         int k = 0;
         auto step = [&](auto S) __attribute__((always_inline)) {
@@ -443,8 +439,6 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
         asm volatile("" : "+v"(ent[0]));
         wait_vmcnt<0>();   // the trailing loads also write LDS
         __syncthreads();
-        if constexpr (BIG)
-            add_bconst<TC, TP, WC, WP, false>(acc, recs);
         if constexpr (KS > 1) {
             v4i *part = (v4i *)lds;
             if (grp == 1) {
@@ -465,7 +459,7 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
             __syncthreads();   // every partial read before the staging overwrites them
         }
     }
-    store_tile<TC, TP, WC, WP, LDS_BYTES, FUSE, BIG>(a, acc, lds, c0, p0, recs);
+    store_tile<TC, TP, WC, WP, LDS_BYTES, FUSE, BIG, true>(a, acc, lds, c0, p0, recs);
 }
 
 // FlowTile -> tile, wave grid, stages, K-step groups, short form.

@@ -663,11 +663,11 @@ __global__ void __launch_bounds__(256) window_sum_tile_kernel(ConvArgs a, int32_
 // Plan preparation: pack w[K][R*S][C] into [Kpad][Jpad] with each tap's
 // channels padded from C to C4 (zeros in the extra channels, the K-tail and
 // the extra rows), and fold bias, term 2 and term 4 into chan[k].bconst.
-// The other chan fields and zpw were uploaded by the host.  One workgroup
-// per (padded) output channel.
+// The other chan fields and zpw were uploaded by the host; krec (or nullptr)
+// gets the channel's KRec.  One workgroup per (padded) output channel.
 __global__ void __launch_bounds__(256) prep_conv_kernel(const int8_t *w, const int32_t *bias, int K, int RS,
                                                         int C, int C4, int Jpad, int32_t zpx, int8_t *wp,
-                                                        ChanRec *chan, const int32_t *zpw)
+                                                        ChanRec *chan, const int32_t *zpw, KRec *krec)
 {
     const int k = blockIdx.x;
     __shared__ long long part[256];
@@ -687,12 +687,19 @@ __global__ void __launch_bounds__(256) prep_conv_kernel(const int8_t *w, const i
             part[threadIdx.x] += part[threadIdx.x + off];
         __syncthreads();
     }
-    if (threadIdx.x == 0 && k < K) {
-        const long long wsum = part[0];
-        const long long b = bias ? (long long)bias[k] : 0;
-        const long long J = (long long)RS * C4;
-        const long long c = b - (long long)zpx * wsum + J * zpx * (long long)zpw[k];
-        chan[k].bconst = (int32_t)(uint32_t)(unsigned long long)c;
+    if (threadIdx.x == 0) {
+        int32_t bconst = 0;
+        if (k < K) {
+            const long long wsum = part[0];
+            const long long b = bias ? (long long)bias[k] : 0;
+            const long long J = (long long)RS * C4;
+            const long long c = b - (long long)zpx * wsum + J * zpx * (long long)zpw[k];
+            bconst = (int32_t)(uint32_t)(unsigned long long)c;
+            chan[k].bconst = bconst;
+        }
+        if (krec)
+            krec[k] = KRec{(long long)bconst * chan[k].mult + ((long long)chan[k].rndzp << 32), chan[k].mult,
+                           chan[k].shift - 32};
     }
 }
 
@@ -817,10 +824,11 @@ hipError_t launch_window_sums(const ConvArgs &a, int32_t *out, hipStream_t st)
 }
 
 hipError_t launch_prep_conv(const int8_t *w, const int32_t *bias, int K, int RS, int C, int C4, int Jpad,
-                            int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, hipStream_t st)
+                            int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, KRec *krec,
+                            hipStream_t st)
 {
     hipLaunchKernelGGL(prep_conv_kernel, dim3(Kpad), dim3(256), 0, st, w, bias, K, RS, C, C4, Jpad, zpx, wp,
-                       chan, zpw);
+                       chan, zpw, krec);
     return hipGetLastError();
 }
 

@@ -257,15 +257,19 @@ __global__ void __launch_bounds__(kSmallWaves * 64, 2) conv_small_kernel(ConvArg
         }
         uint32_t packed = requant4(a, s, rec);
         if constexpr (FUSE) {
-            uint32_t o = 0;
+            if (a.fadd.flt) {
+                packed = residual_add4_f32(a, packed, res);
+            } else {
+                uint32_t o = 0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t xb = (packed >> (8 * e)) & 0xffu, rb = (res >> (8 * e)) & 0xffu;
-                const int t = add_one(a.fadd, a.ydt == 1 ? (int)(int8_t)xb : (int)xb,
-                                      a.rdt == 1 ? (int)(int8_t)rb : (int)rb);
-                o |= ((uint32_t)t & 0xffu) << (8 * e);
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t xb = (packed >> (8 * e)) & 0xffu, rb = (res >> (8 * e)) & 0xffu;
+                    const int t = add_one(a.fadd, a.ydt == 1 ? (int)(int8_t)xb : (int)xb,
+                                          a.rdt == 1 ? (int)(int8_t)rb : (int)rb);
+                    o |= ((uint32_t)t & 0xffu) << (8 * e);
+                }
+                packed = o;
             }
-            packed = o;
         }
         uint8_t *yp = (uint8_t *)a.y + off;
         if (full) {

@@ -5,6 +5,7 @@
 #include "qnn_internal.h"
 
 #include <algorithm>
+#include <cfenv>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -159,6 +160,7 @@ struct qnn_plan {
     ConvArgs conv{};
     int avec = 16, mode = OUT_REQUANT;
     ConvKernel ker;             // kernel family and tile that run_plan launches
+    ConvKernel fuse_ker;        // what ker gives way to when a residual add is fused and ker has none
     bool term3 = false;
     // the conv output's own quantization (the first input of a fused
     // residual add), and whether an add is fused (qnn_plan_set_residual)
@@ -494,6 +496,17 @@ ConvKernel default_kernel(const std::vector<ConvKernel> &c, int64_t M, int K, in
     return has(FAM_FLOW, t) ? ConvKernel{FAM_FLOW, t} : c[0];
 }
 
+// Whether a kernel's epilogue has the fused residual add.
+bool can_fuse(const ConvKernel &k)
+{
+    const int wave_tile = k.fam == FAM_FLOW    ? flow_wave_tile(k.tile)
+                          : k.fam == FAM_SMALL ? 16 * 16
+                          : k.fam == FAM_DMA   ? dma_wave_tile(k.tile)
+                          : k.fam == FAM_TAP   ? tap_wave_tile(k.tile)
+                                               : 0;
+    return wave_tile != 0 && wave_tile <= kFuseMaxWaveTile;
+}
+
 // Tiling of the launched kernel: tile counts, K-steps, persistent grid.
 // The padding correction tables (pcorr_tab, pcls_tab) belong to the
 // LDS-direct kernel only: the other families gather zp_x themselves.
@@ -547,7 +560,8 @@ hipError_t launch_conv_kernel(const ConvArgs &a, const ConvKernel &k, int avec, 
 
 // Times `count` candidate kernels and returns the index of the fastest in
 // *best: launch(i) enqueues candidate i on st (hipSuccess with *ran = false
-// where it does not apply to the shape).
+// where it does not apply to the shape). *order: {median, index} of every one
+// that ran, fastest first.
 //
 // A layer inside a network finds its activations where its producer left
 // them, in the last-level cache, and the L2s full of other layers' lines. So
@@ -560,7 +574,8 @@ hipError_t launch_conv_kernel(const ConvArgs &a, const ConvKernel &k, int avec, 
 // after a 320 MB read that empties the last-level cache too, 750 us with
 // those of launches after a fresh write of the input alone.
 template <typename L>
-qnn_status time_candidates(size_t count, hipStream_t st, int *sink, L launch, size_t *best)
+qnn_status time_candidates(size_t count, hipStream_t st, int *sink, L launch, size_t *best,
+                           std::vector<std::pair<float, size_t>> *order = nullptr)
 {
     constexpr int kRuns = 5, kMore = 8, kFinal = 4;
     const size_t flush_bytes = size_t(64) << 20;
@@ -600,6 +615,8 @@ qnn_status time_candidates(size_t count, hipStream_t st, int *sink, L launch, si
     }
     if (e == hipSuccess && !t.empty()) {
         std::stable_sort(t.begin(), t.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+        if (order)
+            *order = t;
         size_t n = 1;
         while (n < t.size() && n < kFinal && t[n].first < 1.1f * t[0].first)
             ++n;
@@ -633,11 +650,13 @@ qnn_status time_candidates(size_t count, hipStream_t st, int *sink, L launch, si
     return e == hipSuccess ? QNN_OK : hip_fail(e, "kernel tuning");
 }
 
-// Times every candidate on the plan's shape and returns the fastest.
+// Times every candidate on the plan's shape and returns the fastest, and in
+// *fuse_best the fastest that can add a residual (unchanged where none can).
 // Scratch activations (a constant fill), output and window sums are
 // allocated for the measurement and freed again.
 qnn_status autotune_conv(const ConvArgs &base, const std::vector<ConvKernel> &cands, int avec, bool term3,
-                         const int32_t *pcorr_tab, const uint8_t *pcls_tab, hipStream_t st, ConvKernel *best)
+                         const int32_t *pcorr_tab, const uint8_t *pcls_tab, hipStream_t st, ConvKernel *best,
+                         ConvKernel *fuse_best)
 {
     const size_t xb = align_up((size_t)base.N * base.H * base.W * base.C, 256);
     const size_t elem = base.mode == OUT_INT32 ? 4 : 1;
@@ -669,6 +688,7 @@ qnn_status autotune_conv(const ConvArgs &base, const std::vector<ConvKernel> &ca
         s = hip_fail(e, "kernel tuning set-up");
     } else {
         size_t i = cands.size();
+        std::vector<std::pair<float, size_t>> order;
         s = time_candidates(
             cands.size(), st, (int *)buf,
             [&](size_t c, bool *ran) {
@@ -676,9 +696,12 @@ qnn_status autotune_conv(const ConvArgs &base, const std::vector<ConvKernel> &ca
                 *ran = a.ntiles >= 0;
                 return *ran ? launch_conv_kernel(a, cands[c], avec, st) : hipSuccess;
             },
-            &i);
+            &i, &order);
         if (s == QNN_OK && i < cands.size())
             *best = cands[i];
+        for (size_t k = order.size(); k-- > 0;)
+            if (can_fuse(cands[order[k].second]))
+                *fuse_best = cands[order[k].second];
     }
     (void)hipStreamSynchronize(st);
     (void)hipFree(buf);
@@ -1207,6 +1230,11 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     for (int k = 0; k < d.K; ++k)
         if (shift[k] < 33 || shift[k] > 53)
             fast = false;
+    // records with bconst folded into the product (KRec) where no sum without
+    // bconst can leave int32: |x'| and |w| up to 2^7 per product, padding
+    // correction and term 3 up to 2^8 * 2^7
+    const bool krec_ok =
+        fast && flow_ok && Jf * (1 + (pcorr ? 2 : 0) + (term3 ? 2 : 0)) < (int64_t(1) << (31 - 14));
     const bool staged = d.yt != QNN_INT32 && env_int("QNN_STAGED", 1) != 0;
     std::vector<ConvKernel> cands;
     if (rowpack) {
@@ -1234,13 +1262,15 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     const size_t wq_bytes = flow_ok && own_pack ? align_up((size_t)Kpad * fJpad, 256) : 0;
     const size_t wr_bytes = rowpack ? align_up((size_t)Kpad * Jr, 256) : 0;
     const size_t ch_bytes = align_up(sizeof(ChanRec) * Kpad, 256);
+    const size_t kr_bytes = krec_ok ? ch_bytes : 0;
     const size_t zw_bytes = align_up(sizeof(int32_t) * Kpad, 256);
     const size_t pad_bytes = 256;
     const size_t pcls_bytes = pcorr ? align_up((size_t)M, 256) : 0;
     const size_t corr_bytes = pcorr ? align_up(sizeof(int32_t) * ncls * Kpad, 256) : 0;
     const size_t mask_bytes = pcorr ? align_up(sizeof(uint32_t) * 2 * ncls, 256) : 0;
     const size_t total =
-        wp_bytes + wf_bytes + wr_bytes + wq_bytes + ch_bytes + zw_bytes + pad_bytes + pcls_bytes + corr_bytes + mask_bytes;
+        wp_bytes + wf_bytes + wr_bytes + wq_bytes + ch_bytes + kr_bytes + zw_bytes + pad_bytes + pcls_bytes + corr_bytes +
+        mask_bytes;
     hipError_t e = hipMalloc(&p->dev, total);
     if (e != hipSuccess) {
         free_plan(p);
@@ -1250,7 +1280,8 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     int8_t *wf = wf_bytes ? wp + wp_bytes : nullptr;
     int8_t *wr = rowpack ? wp + wp_bytes + wf_bytes : nullptr;
     int8_t *wq = wq_bytes ? wp + wp_bytes + wf_bytes + wr_bytes : nullptr;
-    ChanRec *chan = (ChanRec *)((char *)p->dev + wp_bytes + wf_bytes + wr_bytes + wq_bytes);
+    KRec *krec = kr_bytes ? (KRec *)((char *)p->dev + wp_bytes + wf_bytes + wr_bytes + wq_bytes) : nullptr;
+    ChanRec *chan = (ChanRec *)((char *)p->dev + wp_bytes + wf_bytes + wr_bytes + wq_bytes + kr_bytes);
     int32_t *zpw_d = (int32_t *)((char *)chan + ch_bytes);
     uint8_t *padbuf = (uint8_t *)zpw_d + zw_bytes;
     // channel records, weight zero points and the padding block (zp_x
@@ -1281,7 +1312,7 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
         masks.insert(masks.end(), bc.cmask.begin(), bc.cmask.end());
     }
     if ((e = hipMemcpyAsync(chan, host.data(), host.size(), hipMemcpyHostToDevice, st)) != hipSuccess ||
-        (e = launch_prep_conv(d.w, d.bias, d.K, RS, d.C, C4, Jpad, Kpad, zpx_l, wp, chan, zpw_d, st)) !=
+        (e = launch_prep_conv(d.w, d.bias, d.K, RS, d.C, C4, Jpad, Kpad, zpx_l, wp, chan, zpw_d, krec, st)) !=
             hipSuccess ||
         (wr && (e = launch_rowpack_weights(d.w, d.K, d.R, d.S, d.C, C4, Kpad, Jr, wr, st)) != hipSuccess) ||
         (wq && (e = launch_tap_pack(d.w, d.K, RS, d.C, C16, Kpad, (int)fJpad, wq, st)) != hipSuccess) ||
@@ -1325,6 +1356,8 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     a.lo_off = lo + off8;
     a.hi_off = hi + off8;
     a.out_xor = off8 ? 0x80808080u : 0u;
+    a.krec = krec;
+    a.sat_pack = a.lo_off <= 0 && a.hi_off >= 255;
     a.staged = staged;
     a.zp4 = 0x01010101u * (uint32_t)(uint8_t)zpx_l;
     const int32_t *pcorr_tab = pcorr ? corr_d : nullptr;
@@ -1412,10 +1445,17 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     if (timed.size() > 1) {
         if (timed[0].fam == FAM_FLOW || timed[0].fam == FAM_SMALL)
             best = default_kernel(timed, M, d.K, (int)((Jf + 63) / 64));
+        std::vector<ConvKernel> fusable;
+        for (const ConvKernel &k : timed)
+            if (k.fam == FAM_FLOW && can_fuse(k))
+                fusable.push_back(k);
+        if (!fusable.empty())
+            p->fuse_ker = default_kernel(fusable, M, d.K, (int)((Jf + 63) / 64));
         if (M > 0 && env_int("QNN_AUTOTUNE", 1) != 0) {
             const std::string key = tune_key(d, term3, ncls, fast);
             if (!tune_lookup(key, cands, &best) && tune) {
-                if ((s = autotune_conv(a, timed, p->avec, term3, pcorr_tab, pcls_tab, st, &best)) != QNN_OK) {
+                if ((s = autotune_conv(a, timed, p->avec, term3, pcorr_tab, pcls_tab, st, &best,
+                                       &p->fuse_ker)) != QNN_OK) {
                     free_plan(p);
                     return s;
                 }
@@ -2070,6 +2110,39 @@ qnn_status qnn_add(void *stream, const void *a, qnn_dtype a_dtype, qnn_qparams a
     return e == hipSuccess ? QNN_OK : hip_fail(e, "add launch");
 }
 
+// One term of the add, round((x - zp) * mult / 2^shift) + plus for the bytes x
+// of a dtype, as rint(fma(u, *m, *c)) in f32, u the byte as uint8 (int8: x +
+// 128): *c is the middle of what keeps every u's value nearest to its term.
+// Returns whether it gives all 256 terms (and their sums are exact in f32).
+static bool fit_float_term(bool is_int8, int32_t zp, int32_t mult, int32_t shift, int32_t rounding, int32_t plus,
+                           float *m, float *c)
+{
+    if (std::fegetround() != FE_TONEAREST)
+        return false;   // the check below would not be the device's arithmetic
+    const float near = (float)std::ldexp((double)mult, -shift);
+    int64_t term[256];
+    for (int u = 0; u < 256; ++u) {
+        term[u] = rounding_mul_shift((is_int8 ? u - 128 : u) - zp, mult, shift, rounding) + plus;
+        if (term[u] <= -(1 << 22) || term[u] >= (1 << 22))
+            return false;
+    }
+    for (const float f : {near, std::nextafterf(near, 0.0f), std::nextafterf(near, 1e30f)}) {
+        double least = -1e30, most = 1e30;
+        for (int u = 0; u < 256; ++u) {
+            least = std::max(least, (double)term[u] - 0.5 - (double)u * (double)f);
+            most = std::min(most, (double)term[u] + 0.5 - (double)u * (double)f);
+        }
+        *m = f;
+        *c = (float)(0.5 * (least + most));
+        bool same = true;
+        for (int u = 0; u < 256 && same; ++u)
+            same = std::nearbyintf(std::fmaf((float)u, *m, *c)) == (float)term[u];
+        if (same)
+            return true;
+    }
+    return false;
+}
+
 qnn_status qnn_plan_set_residual(qnn_plan *plan, qnn_dtype r_dtype, qnn_qparams r_q, int32_t r_ldc, int32_t r_coff,
                                  qnn_dtype o_dtype, qnn_qparams o_q, qnn_clamp act, qnn_rounding rounding)
 {
@@ -2080,12 +2153,10 @@ qnn_status qnn_plan_set_residual(qnn_plan *plan, qnn_dtype r_dtype, qnn_qparams 
     if (plan->fused)
         return fail(QNN_ERR_UNSUPPORTED, "plan_set_residual: the plan already adds a residual");
     const ConvArgs &c = plan->conv;
-    const int wave_tile = plan->ker.fam == FAM_FLOW    ? flow_wave_tile(plan->ker.tile)
-                          : plan->ker.fam == FAM_SMALL ? 16 * 16
-                          : plan->ker.fam == FAM_DMA ? dma_wave_tile(plan->ker.tile)
-                          : plan->ker.fam == FAM_TAP ? tap_wave_tile(plan->ker.tile)
-                                                     : 0;
-    if (plan->mode != OUT_REQUANT || !c.staged || wave_tile == 0 || wave_tile > kFuseMaxWaveTile)
+    // the 256 x 256 tile has no fused add: such a plan turns to the fastest
+    // tile that has one (fuse_ker), once everything else is in order
+    const ConvKernel ker = plan->ker.fam == FAM_FLOW && !can_fuse(plan->ker) ? plan->fuse_ker : plan->ker;
+    if (plan->mode != OUT_REQUANT || !c.staged || !can_fuse(ker))
         return fail(QNN_ERR_UNSUPPORTED,
                     "plan_set_residual: the plan's kernel has no fused-add epilogue (8-bit output staged by the "
                     "tap-walk or LDS-direct kernels whose waves hold at most 64 x 64 outputs)");
@@ -2107,8 +2178,23 @@ qnn_status qnn_plan_set_residual(qnn_plan *plan, qnn_dtype r_dtype, qnn_qparams 
     qnn_status s = make_add_args((qnn_dtype)plan->y_dt, y_q, r_dtype, r_q, o_dtype, o_q, act, rounding, &args);
     if (s != QNN_OK)
         return s;
-    // term tables (one term per operand byte) where they are exact
-    if (args.tab_ok) {
+    // both terms in f32 where that gives every byte's term; else term tables
+    // (one term per operand byte) where they are exact
+    {
+        const int32_t off = o_dtype == QNN_INT8 ? 128 : 0;
+        args.flt = fit_float_term(plan->y_dt == QNN_INT8, args.zpa, args.ma, args.na, args.rounding, 0, &args.fma_a,
+                                  &args.fca) &&
+                   fit_float_term(r_dtype == QNN_INT8, args.zpb, args.mb, args.nb, args.rounding, args.zp_y + off,
+                                  &args.fma_b, &args.fcb);
+        args.uxa = plan->y_dt == QNN_INT8 ? 0x80808080u : 0u;
+        args.uxb = r_dtype == QNN_INT8 ? 0x80808080u : 0u;
+        args.uy = off ? 0x80808080u : 0u;
+        args.flo = (float)(args.lo + off);
+        args.fhi = (float)(args.hi + off);
+        if (env_int("QNN_FLOAT_ADD", 1) == 0)
+            args.flt = 0;
+    }
+    if (args.tab_ok && !args.flt) {
         hipError_t e;
         if ((e = hipMalloc((void **)&plan->addtab, 512 * sizeof(int32_t))) != hipSuccess) {
             plan->addtab = nullptr;
@@ -2123,12 +2209,21 @@ qnn_status qnn_plan_set_residual(qnn_plan *plan, qnn_dtype r_dtype, qnn_qparams 
         }
         args.tab = plan->addtab;
     }
+    if (ker.fam != plan->ker.fam || ker.tile != plan->ker.tile) {
+        plan->ker = ker;
+        set_tiling(plan->conv, ker, plan->avec, nullptr, nullptr);   // no padding corrections (1x1 filters)
+        const TileShape ts = kernel_shape(ker);
+        char buf[120];
+        snprintf(buf, sizeof buf, "conv_dma_flow tile=%dx%dx%d threads=%d stages=%d%s tiles=%d", ts.tc, ts.tp, ts.bk,
+                 flow_threads(ker.tile), flow_stages(ker.tile), flow_short(ker.tile) ? "s" : "", plan->conv.ntiles);
+        plan->desc = buf + plan->desc.substr(plan->desc.find(" term3="));
+    }
     plan->conv.fadd = args;
     plan->conv.r_ldc = r_ldc;
     plan->conv.r_coff = r_coff;
     plan->conv.rdt = r_dtype == QNN_INT8 ? 1 : 0;
     plan->fused = true;
-    plan->desc += args.tab ? " +add" : " +add(no-tables)";
+    plan->desc += args.tab || args.flt ? " +add" : " +add(no-tables)";
     return QNN_OK;
 }
 

@@ -47,6 +47,16 @@ struct ChanRec {
     int32_t mult, bconst, rndzp, shift;
 };
 
+// The same channel with bconst and the rounding in one 64-bit addend, for
+// plans whose sums without bconst stay within int32: the output before the
+// clamp is the high word of acc * mult + k, shifted right by sh = shift - 32;
+// k = bconst * mult + (rndzp << 32).
+struct KRec {
+    long long k;
+    int32_t mult, sh;
+};
+static_assert(sizeof(KRec) == sizeof(ChanRec), "staged as the same 16 bytes per channel");
+
 enum OutMode { OUT_REQUANT = 0, OUT_INT32 = 1 };
 
 // Fixed-point requantize of v: round(v * mult / 2^shift) with a 64-bit
@@ -64,7 +74,7 @@ enum OutMode { OUT_REQUANT = 0, OUT_INT32 = 1 };
 // elementwise kernels take the early HALF_UP return (EARLY = true), the
 // conv epilogues the single shared rounding.
 template <bool EARLY = false>
-__device__ __forceinline__ long long rounding_mul_shift(int v, int mult, int shift, int mode)
+__host__ __device__ __forceinline__ long long rounding_mul_shift(int v, int mult, int shift, int mode)
 {
     long long p = (long long)v * (long long)mult;
     if constexpr (EARLY) {
@@ -148,6 +158,14 @@ struct AddArgs {
     // by add_table_kernel), so that an element's sum is clamp(tab[x] +
     // tab[256 + r]); nullptr where a 32-bit sum could overflow
     const int32_t *tab;
+    // fused residual add only: flt: both terms are rint(fma(u, m, c)) in f32
+    // for every operand byte u (checked one by one when the plan is told of
+    // the residual), u the byte as uint8 after ^ ux (int8 operands: 0x80), the
+    // second term plus zp_y and the output's offset; flo / fhi: the clamp with
+    // that offset, uy: the flip that takes it off the packed output again
+    int32_t flt;
+    float fma_a, fca, fma_b, fcb, flo, fhi;
+    uint32_t uxa, uxb, uy;
 };
 
 // round(v * mult / 2^shift), ties up, for |v| < 2^9 and shift = np + 16 with
@@ -236,6 +254,8 @@ struct ConvArgs {
     // 16-byte chunks per tap, magic divisors by that, by S and by tiles_c,
     // pixel tiles whose channel tiles are interleaved
     const int8_t *fw;
+    const KRec *krec;       // [Kpad], or nullptr: chan
+    int32_t sat_pack;       // krec: the clamp is the byte's own range
     int32_t fJpad, fJ;
     int32_t linear, Cq, gp;
     uint32_t mCq, sCq, mS, sS, mTC, sTC;
@@ -487,7 +507,7 @@ hipError_t launch_window_sums(const ConvArgs &a, int32_t *out, hipStream_t st);
 hipError_t launch_pad_channels(const uint8_t *x, uint8_t *xp, long long pixels, int C, int C4, uint8_t zp,
                                hipStream_t st);
 hipError_t launch_prep_conv(const int8_t *w, const int32_t *bias, int K, int RS, int C, int C4, int Jpad,
-                            int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, hipStream_t st);
+                            int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, KRec *krec, hipStream_t st);
 hipError_t launch_prep_dw(const int8_t *w, const int32_t *bias, int RS, int C, const int32_t *zpw, int32_t *wq,
                           ChanRec *chan, hipStream_t st);
 hipError_t launch_depthwise(const DwArgs &a, hipStream_t st);
