@@ -11,7 +11,9 @@
 // pixel; neighbouring threads take neighbouring channel groups, so each
 // window cell is one coalesced row segment.  The kernel is bound by HBM
 // traffic: every input byte once for non-overlapping windows (overlapping
-// ones re-read from L2), every output byte once.
+// ones re-read from L2), every output byte once; 3x3 average pooling at stride
+// 1 is bound by its instructions instead and has a kernel of its own
+// (avg3_kernel).
 #include "qnn_internal.h"
 
 namespace qnn {
@@ -173,6 +175,109 @@ __global__ void __launch_bounds__(256) pool_kernel(PoolArgs a)
     }
 }
 
+// 3x3 average at stride 1, 16 channels per thread and T output rows of one
+// column. pool_kernel spends about 450 vector instructions on 16 outputs (byte
+// selects, nine cells added one by one, an exact division each), which is what
+// bounds it: 35x35x192 batch 64 18.1 us, 35x35x256 22.7 us. Here the three
+// cells of a window row are added once for the up to three outputs that hold
+// them, cells outside the input are loads out of the buffer's range (zeros),
+// and a division is one 24-bit multiply-add whose byte 2 is the quotient:
+// 9.3 and 11.7 us, the Inception mixed-5 body 198 -> 183 us.
+//
+// With U the window's sum as uint8 values (int8 plus 128) the quotient is
+// floor((2U + cnt) / (2 cnt)), less one in the numerator for negative sums
+// under ties away from zero. floor(n / d) = (n * M) >> 16 with M = ceil(2^16 /
+// d) holds while n * (M * d - 2^16) < 2^16: checked for d = 2 cnt, n <= 511
+// cnt, cnt = 1, 2, 3, 4, 6 and 9 (the products below 24528).
+template <bool SIGNED, int T>
+__global__ void __launch_bounds__(256) avg3_kernel(PoolArgs a, int hb)
+{
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    const unsigned groups = (unsigned)(a.C / 16);
+    const unsigned total = (unsigned)a.N * (unsigned)hb * (unsigned)a.Wo * groups;
+    const unsigned u = blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= total)
+        return;
+    const unsigned g = u % groups;
+    unsigned p = u / groups;
+    const int ow = (int)(p % (unsigned)a.Wo);
+    p /= (unsigned)a.Wo;
+    const int oh0 = (int)(p % (unsigned)hb) * T;
+    const int n = (int)(p / (unsigned)hb);
+    const int h0 = oh0 - a.pt, w0 = ow - a.pl;
+    const int base = ((n * a.H + h0) * a.W + w0) * a.C + (int)g * 16;
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc((void *)a.x, (short)0, a.N * a.H * a.W * a.C, 0x00020000);
+    bool cv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        cv[c] = (unsigned)(w0 + c) < (unsigned)a.W;
+    const int cols = (int)cv[0] + (int)cv[1] + (int)cv[2];
+    u4 w[T + 2][3];
+#pragma unroll
+    for (int r = 0; r < T + 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const bool in = cv[c] && (unsigned)(h0 + r) < (unsigned)a.H;
+            w[r][c] = __builtin_amdgcn_raw_buffer_load_b128(rx, in ? base + (r * a.W + c) * a.C : (int)0x80000000, 0, 0);
+        }
+    unsigned even[T + 2][4], odd[T + 2][4];   // bytes 0 and 2, 1 and 3 of each word
+#pragma unroll
+    for (int r = 0; r < T + 2; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned f = SIGNED ? 0x80808080u : 0u;
+            const unsigned x0 = w[r][0][k] ^ f, x1 = w[r][1][k] ^ f, x2 = w[r][2][k] ^ f;
+            even[r][k] = (x0 & 0x00ff00ffu) + (x1 & 0x00ff00ffu) + (x2 & 0x00ff00ffu);
+            odd[r][k] = ((x0 >> 8) & 0x00ff00ffu) + ((x1 >> 8) & 0x00ff00ffu) + ((x2 >> 8) & 0x00ff00ffu);
+        }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (oh0 + t >= a.Ho)
+            break;
+        int rows = 0;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            rows += (unsigned)(h0 + t + r) < (unsigned)a.H;
+        const int in = rows * cols, out = 9 - in;
+        const int cnt = a.count_pad ? 9 : in;
+        const int m = cnt == 9   ? 3641
+                      : cnt == 6 ? 5462
+                      : cnt == 4 ? 8192
+                      : cnt == 3 ? 10923
+                      : cnt == 2 ? 16384
+                                 : 32768;
+        // cells outside: added as 0 (uint8) or 128 (int8)
+        const int adj = (SIGNED ? -128 * out : 0) + (a.count_pad ? out * (a.zp + (SIGNED ? 128 : 0)) : 0);
+        const unsigned m2 = 2u * (unsigned)m, c2 = (unsigned)(cnt * m + 2 * m * adj);
+        const unsigned neg = SIGNED && a.rounding == 1 ? (unsigned)(128 * cnt - adj) : 0u;   // sums below it are negative
+        auto div = [&](unsigned s) { return __umul24(s, m2) + (SIGNED && s < neg ? c2 - (unsigned)m : c2); };
+        u4 o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned e = even[t][k] + even[t + 1][k] + even[t + 2][k];
+            const unsigned d = odd[t][k] + odd[t + 1][k] + odd[t + 2][k];
+            const unsigned lo = __builtin_amdgcn_perm(div(d & 0xffffu), div(e & 0xffffu), 0x0c0c0602u);
+            const unsigned hi = __builtin_amdgcn_perm(div(d >> 16), div(e >> 16), 0x06020c0cu);
+            o[k] = (lo | hi) ^ (SIGNED ? 0x80808080u : 0u);
+        }
+        uint8_t *dst = (uint8_t *)a.y + ((size_t)(n * a.Ho + oh0 + t) * a.Wo + ow) * a.C + g * 16;
+        __builtin_nontemporal_store(o, (u4 *)dst);
+    }
+}
+
+template <bool SIGNED>
+static void launch_avg3(const PoolArgs &a, hipStream_t s)
+{
+    // four rows per thread while that leaves two waves per SIMD of 256 CUs
+    const long long per_row = (long long)a.N * a.Wo * (a.C / 16);
+    const int hb4 = (a.Ho + 3) / 4;
+    if (per_row * hb4 >= 131072)
+        launch_main((avg3_kernel<SIGNED, 4>), dim3((unsigned)((per_row * hb4 + 255) / 256)), dim3(256), 0, s, a, hb4);
+    else
+        launch_main((avg3_kernel<SIGNED, 1>), dim3((unsigned)((per_row * a.Ho + 255) / 256)), dim3(256), 0, s, a, a.Ho);
+}
+
 // Few output pixels with large windows (global pooling): a workgroup of
 // SPLIT_WAVES waves takes one output pixel and 64*V channels; wave k sums
 // the window's cells k, k + SPLIT_WAVES, ... and the partial results meet
@@ -304,6 +409,11 @@ hipError_t launch_pool(const PoolArgs &a, bool is_signed, int vec, hipStream_t s
     const long long threads = (long long)a.N * a.Ho * a.Wo * (a.C / vec);
     if (threads == 0)
         return hipSuccess;
+    if (a.mode == 0 && vec == 16 && a.R == 3 && a.S == 3 && a.sh == 1 && a.sw == 1) {
+        if (is_signed) launch_avg3<true>(a, s);
+        else launch_avg3<false>(a, s);
+        return hipGetLastError();
+    }
     long long blocks = (threads + 255) / 256;
     const long long cap = 256LL * 32;
     if (blocks > cap) blocks = cap;
