@@ -17,7 +17,7 @@ size_t flow_lds_bytes(int tile, int nk, bool linear)
 {
     const FlowCfg &c = kFlowCfg[tile];
     const size_t ring = (size_t)c.ns * (c.tc + c.tp) * 64, stage = (size_t)c.tp * (c.tc + 16);
-    return (ring > stage ? ring : stage) + c.tc * sizeof(ChanRec) + (linear ? 0 : (size_t)(nk + 2 * c.ns) * 32) +
+    return (ring > stage ? ring : stage) + (c.tc + 63) / 64 * 64 * sizeof(ChanRec) + (linear ? 0 : (size_t)(nk + 2 * c.ns) * 32) +
            (flow_fuse_cfg(tile) ? 512 * sizeof(int32_t) : 0);
 }
 

@@ -116,19 +116,27 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
     constexpr int WTC = TC / WC, WTP = TP / WP;
     constexpr int FC = WTC / 16, FP = WTP / 16;
     constexpr int STAGE = (TC + TP) * BK;
-    constexpr int LA = TC / (16 * NW), LB = TP / (16 * NW);
+    // 96-channel tiles: of 96 channels, 64-wide tiles compute 128. 1x1 16 -> 96
+    // at 112x112 batch 64 36.1 -> 30.1 us, 3x3 96 -> 96 at 35x35 batch 64 21.6 ->
+    // 20.8 us, the Inception mixed-5 body 183 -> 176.5 us.
+    // Blocks of 16 rows that each wave loads; where the waves don't divide the
+    // channel blocks (96 channels), the last waves load two of them once more,
+    // the same bytes to the same place, so that every wave counts alike
+    constexpr int BLKA = TC / 16;
+    constexpr int LA = (BLKA + NW - 1) / NW, LB = TP / (16 * NW);
     constexpr int LPS = LA + LB;
     constexpr int NSG = NS / KS;
     constexpr bool BIG = WTC * WTP >= 128 * 64;   // no registers for two sets of fragments
     constexpr int LDS_BYTES = NS * STAGE > TP * (TC + 16) ? NS * STAGE : TP * (TC + 16);
-    static_assert(TC % (16 * NW) == 0 && TP % (16 * NW) == 0, "every wave loads whole 16-row blocks");
+    static_assert(TC % 16 == 0 && BLKA >= NW && TP % (16 * NW) == 0, "every wave loads whole 16-row blocks");
+    static_assert(TC % (16 * WC) == 0, "whole 16-channel blocks per wave");
     static_assert(KS == 1 || (KS == 2 && !SHORT && NW * FC * FP * 1024 <= LDS_BYTES), "two groups: ring form");
     static_assert(SHORT ? NS <= 4 : NSG == 4, "ring of four stages per group");
     static_assert(LPS * (SHORT ? NS - 1 : NSG - 2) < 64, "vmcnt range");
     static_assert(FC + FP + 1 <= 15, "reads of one step exceed the lgkmcnt range");
 
     __shared__ __attribute__((aligned(1024))) int8_t lds[LDS_BYTES];
-    __shared__ __attribute__((aligned(16))) ChanRec recs[TC];
+    __shared__ __attribute__((aligned(16))) ChanRec recs[(TC + 63) / 64 * 64];
     extern __shared__ __attribute__((aligned(16))) int8_t dyn_lds[];   // TAB: the chunk table
 
     const int tid = threadIdx.x;
@@ -167,7 +175,7 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
         const __amdgpu_buffer_rsrc_t rc =
             __builtin_amdgcn_make_buffer_rsrc(a.krec ? (void *)a.krec : (void *)a.chan, (short)0, a.Kpad * (int)sizeof(ChanRec), kBufFlags);
 #pragma unroll
-        for (int q = 0; q < TC / 64; ++q)
+        for (int q = 0; q < (TC + 63) / 64; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (__attribute__((address_space(3))) void *)(recs + q * 64), 16,
                                                      (c0 + q * 64 + lane) * (int)sizeof(ChanRec), 0, 0, 0);
     }
@@ -176,10 +184,11 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
     // L % 4, logical chunk (L % 4) ^ sw64(row)
     const int r16 = lane >> 2;
     const int lch = (lane & 3) ^ sw64(r16);
+    auto blkA = [&](int i) { return BLKA % NW == 0 || i < LA - 1 ? i * NW + wave : (i * NW + wave) % BLKA; };
     int voffA[LA];
 #pragma unroll
     for (int i = 0; i < LA; ++i)
-        voffA[i] = (c0 + (i * NW + wave) * 16 + r16) * a.fJpad + lch * 16;
+        voffA[i] = (c0 + blkA(i) * 16 + r16) * a.fJpad + lch * 16;
     int pbase[LB];
     uint32_t pmask[LB];
 #pragma unroll
@@ -238,7 +247,7 @@ __global__ void __launch_bounds__(WC *WP * 64 * KS, (flow_occupancy<TC / WC, TP 
         }
 #pragma unroll
         for (int i = 0; i < LA; ++i)
-            dma16(rw, base + i * NW * 16 * BK, voffA[i], soff);
+            dma16(rw, base + (blkA(i) - wave) * 16 * BK, voffA[i], soff);
 #pragma unroll
         for (int i = 0; i < LB; ++i)
             dma16(rx, base + (TC + i * NW * 16) * BK, voffB[i], TAB ? 0 : soff);
@@ -474,7 +483,8 @@ inline constexpr FlowCfg kFlowCfg[FLOW_COUNT] = {
     {128, 128, 2, 2, 8, 2, false}, {64, 64, 2, 2, 1, 1, true},    {64, 128, 2, 2, 1, 1, true},
     {128, 64, 2, 2, 1, 1, true},   {64, 64, 2, 2, 2, 1, true},    {64, 128, 2, 2, 2, 1, true},
     {128, 64, 2, 2, 2, 1, true},   {64, 64, 2, 2, 4, 1, true},    {64, 128, 2, 2, 4, 1, true},
-    {128, 128, 2, 2, 4, 1, true},
+    {128, 128, 2, 2, 4, 1, true},  {96, 64, 2, 2, 4, 1, false},   {96, 128, 2, 2, 4, 1, false},
+    {96, 128, 2, 2, 1, 1, true},   {96, 128, 2, 2, 2, 1, true},
 };
 constexpr bool flow_fuse_cfg(int t)
 {

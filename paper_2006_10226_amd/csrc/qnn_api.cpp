@@ -440,6 +440,11 @@ void add_flow_candidates(std::vector<ConvKernel> &c, int64_t M, int K, int nk, b
     const int f = env_int("QNN_FLOW", -1), fs = env_int("QNN_SMALL", -1);
     const size_t lds = (size_t)device_lds_per_block();
     auto fits = [&](int t) {
+        // 96 channels: where they round K up no further than 64 do, and stay
+        // inside the padded tables
+        const int tc = flow_tile_shape(t).tc, up = (K + tc - 1) / tc * tc;
+        if (tc == 96 && (up > (K + 63) / 64 * 64 || up > (int)align_up((size_t)K, 256)))
+            return false;
         return (!flow_short(t) || nk <= flow_stages(t)) && (t != FLOW_256x256 || (linear && !term3)) &&
                flow_lds_bytes(t, nk, linear) <= lds;
     };

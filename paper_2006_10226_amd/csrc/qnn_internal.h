@@ -420,6 +420,11 @@ enum FlowTile {
     FLOW_64x64_R4 = 16,
     FLOW_64x128_R4 = 17,
     FLOW_128x128_R4 = 18,
+    // channel counts that 64-wide tiles would round up further
+    FLOW_96x64 = 19,
+    FLOW_96x128 = 20,
+    FLOW_96x128_R1 = 21,
+    FLOW_96x128_R2 = 22,
     FLOW_COUNT
 };
 TileShape flow_tile_shape(int tile);
