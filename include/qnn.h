@@ -394,8 +394,12 @@ qnn_status qnn_time_next_kernel(void *start_event, void *stop_event);
  * multiples of 16 accept it;
  * others, int32 outputs and a second call return QNN_ERR_UNSUPPORTED and
  * leave the plan as it was.  r_ldc >= r_coff + K.  A fused plan runs only
- * through qnn_plan_run_residual.  Where the add's per-byte terms fit 32-bit
- * sums, the call tabulates them in a 2 KB device buffer that the plan owns
+ * through qnn_plan_run_residual.  A plan whose own choice is the largest
+ * tile, which has no fused epilogue, turns to the fastest of its candidates
+ * that has one (qnn_plan_describe changes with it).  Where an f32
+ * multiply-add gives every per-byte term of the add exactly, nothing is
+ * allocated; else, where the terms fit 32-bit sums, the call tabulates them
+ * in a 2 KB device buffer that the plan owns
  * (allocated here, one small kernel launched on the null stream and
  * waited for); QNN_ERR_ALLOC or QNN_ERR_HIP if that fails, the plan as it
  * was.

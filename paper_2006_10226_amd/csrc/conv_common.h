@@ -352,8 +352,6 @@ __device__ __forceinline__ void add_bconst(v4i (&acc)[TC / WC / 16][TP / WP / 16
 #pragma unroll
             for (int j = 0; j < FP; ++j)
                 acc[i][j] += b;
-            if constexpr (FC * FP > 16)
-                lds_settled(acc[i]);   // these sums before the next records are read
         }
     }
 }
