@@ -34,6 +34,9 @@ _CONV = re.compile(r"conv_mfma_kernel<(\d+), ?(\d+), ?(\d+), ?(\d+), ?(\d+), ?(\
 _TAP = re.compile(r"conv_tap_kernel<(\d+), ?(\d+), ?(\d+), ?(\d+), ?(\d+)(?:, ?(true|false))?>")
 _DMA = re.compile(r"conv_dma_kernel<(\d+), ?(\d+), ?(\d+), ?(\d+), ?(\d+), ?(true|false), ?(true|false)"
                   r"(?:, ?(\d+))?(?:, ?(true|false))?(?:, ?(true|false))?>")
+_FLOW = re.compile(r"conv_flow_kernel<(\d+), ?(\d+), ?(\d+), ?(\d+), ?(\d+), ?(\d+), ?(true|false), ?(?:true|false), "
+                   r"?(?:true|false), ?(true|false)>")
+_SMALL = re.compile(r"conv_small_kernel<(\d+), ?(\d+), ?(?:true|false), ?(?:true|false), ?(true|false)>")
 _WAVE = re.compile(r"conv_wave_kernel<(\d+), ?(\d+), ?(true|false)>")
 _HALO = re.compile(r"conv_halo_kernel<(\d+), ?(true|false)>")
 _WIN = re.compile(r"conv_window_kernel<(\d+), ?(\d+), ?(\d+), ?(true|false)>")
@@ -74,6 +77,16 @@ def group_of(kernel_name):
         split = " ksplit" if m.group(9) == "true" else ""
         fused = " +add" if m.group(10) == "true" else ""
         return f"conv_dma tile={tc}x{tp}x64 threads={wc * wp * ks * 64} stages={ns}{short}{split}{fused}"
+    m = _FLOW.search(kernel_name)
+    if m:
+        tc, tp, wc, wp, ns, ks = (int(v) for v in m.groups()[:6])
+        short = "s" if m.group(7) == "true" else ""
+        fused = " +add" if m.group(8) == "true" else ""
+        return f"conv_dma_flow tile={tc}x{tp}x64 threads={wc * wp * ks * 64} stages={ns}{short}{fused}"
+    m = _SMALL.search(kernel_name)
+    if m:
+        fused = " +add" if m.group(3) == "true" else ""
+        return f"conv_dma_small tile={16 * int(m.group(1))}x{16 * int(m.group(2))}x64 threads=512 stages=1{fused}"
     m = _WAVE.search(kernel_name)
     if m:
         split = int(m.group(1))
