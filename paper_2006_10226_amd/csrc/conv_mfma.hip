@@ -688,18 +688,21 @@ __global__ void __launch_bounds__(256) prep_conv_kernel(const int8_t *w, const i
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        int32_t bconst = 0;
+        // The true sum fits int32, the constant alone need not (channels
+        // padded to C4 take part in it): bconst is added modulo 2^32, KRec::k
+        // modulo 2^64, each exact for the sum.
+        long long c = 0;
         if (k < K) {
             const long long wsum = part[0];
             const long long b = bias ? (long long)bias[k] : 0;
             const long long J = (long long)RS * C4;
-            const long long c = b - (long long)zpx * wsum + J * zpx * (long long)zpw[k];
-            bconst = (int32_t)(uint32_t)(unsigned long long)c;
-            chan[k].bconst = bconst;
+            c = b - (long long)zpx * wsum + J * zpx * (long long)zpw[k];
+            chan[k].bconst = (int32_t)(uint32_t)(unsigned long long)c;
         }
         if (krec)
-            krec[k] = KRec{(long long)bconst * chan[k].mult + ((long long)chan[k].rndzp << 32), chan[k].mult,
-                           chan[k].shift - 32};
+            krec[k] = KRec{(long long)((unsigned long long)c * (unsigned long long)(long long)chan[k].mult +
+                                       ((unsigned long long)(uint32_t)chan[k].rndzp << 32)),
+                           chan[k].mult, chan[k].shift - 32};
     }
 }
 

@@ -50,7 +50,7 @@ struct ChanRec {
 // The same channel with bconst and the rounding in one 64-bit addend, for
 // plans whose sums without bconst stay within int32: the output before the
 // clamp is the high word of acc * mult + k, shifted right by sh = shift - 32;
-// k = bconst * mult + (rndzp << 32).
+// k = c * mult + (rndzp << 32), c the constant before it is wrapped to bconst.
 struct KRec {
     long long k;
     int32_t mult, sh;

@@ -87,3 +87,27 @@ def test_largest_tile_gives_way(tmp_path):
     y = p.run(dev(c.x), residual=dev(r)).cpu().numpy()
     p.close()
     assert_equal(y, O.add(mid, c.s_y, c.zp_y, r, 0.03, 7, 0.05, 9, "u8"), "fused after giving way")
+
+
+@pytest.mark.parametrize("knob", [dict(QNN_FLOW=0), dict(QNN_FLOW=3), dict(QNN_SMALL=0), dict(QNN_TILE=0)],
+                         ids=lambda d: "".join(f"{k[4:].lower()}{v}" for k, v in d.items()))
+@pytest.mark.parametrize("R", [1, 3])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_constant_outside_int32(R, sign, knob):
+    """One input channel, padded to four, with weight zero points and the
+    largest bias that is accepted: every sum fits int32, the constant that
+    bias, zero points and padded channels fold into does not."""
+    K, w_v, zp_w = 20, (127, -128)[sign < 0], (-128, 127)[sign < 0]
+    bias = sign * (2**31 - 1 - 255 * 255 * R * R)
+    assert abs(bias + 128 * w_v * R * R + 4 * R * R * -128 * zp_w) > 2**31   # x less 128 has zero point -128
+    rng = np.random.default_rng(R)
+    x = rng.integers(0, 256, size=(2, 7, 9, 1)).astype(np.uint8)
+    x[0, 0, :2, 0] = 0, 255
+    w = np.full((K, R, R, 1), w_v, np.int8)
+    zpw, b = np.full(K, zp_w, np.int32), np.full(K, bias, np.int32)
+    s_w, pad = np.full(K, 2.0**-23, np.float32), R // 2     # shift 53, the largest of the 32-bit form
+    with env(**knob):
+        y = Q.conv2d(dev(x), 1.0, 0, dev(w), s_w, zpw, dev(b), 1, pad, 1, 1.0, 128, "u8").cpu().numpy()
+    ref = O.conv2d(x, 1.0, 0, w, s_w, zpw, b, 1.0, 128, "u8", pads=(pad,) * 4)
+    assert (ref == (255 if sign > 0 else 0)).all()
+    assert_equal(y, ref, f"constant beyond int32: {knob} {R}x{R}")
