@@ -1,44 +1,11 @@
 // LDS-direct implicit-GEMM conv launches (kernel in conv_dma_kernel.h) and
-// the plan-time kernels of that family: border-class correction table,
-// row-pair weight packing, zero-point padded image copies.
+// the plan-time kernels of that family: row-pair weight packing, zero-point
+// padded image copies.
 #include "conv_dma_kernel.h"
 
 #include <algorithm>
 
 namespace qnn {
-
-// Padding correction table of the border classes (plan preparation): one
-// thread per (class, channel) sums the packed weights of the taps outside
-// the image and scales by zp_x.  The result wraps to int32 like every other
-// term of the accumulator, which is exact whenever the final sum fits.
-__global__ void __launch_bounds__(256) border_corr_kernel(const int8_t *wp, int Kpad, int Jpad, int C4, int S, int RS,
-                                                          const uint32_t *rmask, const uint32_t *cmask, int ncls,
-                                                          int32_t zpx, int32_t *corr)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= ncls * Kpad)
-        return;
-    const int cls = idx / Kpad, k = idx - cls * Kpad;
-    long long sum = 0;
-    for (int t = 0; t < RS; ++t) {
-        const int r = t / S, s = t - r * S;
-        if (((rmask[cls] >> r) & (cmask[cls] >> s) & 1u) == 0) {
-            const int8_t *row = wp + (size_t)k * Jpad + (size_t)t * C4;
-            for (int c = 0; c < C4; ++c)
-                sum += row[c];
-        }
-    }
-    corr[idx] = (int32_t)(uint32_t)(unsigned long long)(sum * zpx);
-}
-
-hipError_t launch_border_corr(const int8_t *wp, int Kpad, int Jpad, int C4, int S, int RS, const uint32_t *rmask,
-                              const uint32_t *cmask, int ncls, int32_t zpx, int32_t *corr, hipStream_t st)
-{
-    const int n = ncls * Kpad;
-    hipLaunchKernelGGL(border_corr_kernel, dim3((n + 255) / 256), dim3(256), 0, st, wp, Kpad, Jpad, C4, S, RS, rmask,
-                       cmask, ncls, zpx, corr);
-    return hipGetLastError();
-}
 
 // Row-pair packing of the weights for small channel counts (S * C4 <= 32):
 // wp[k][64 s + 32 h + b] = w[k][r][b / C4][b % C4] for filter row r = 2 s + h,

@@ -660,24 +660,89 @@ __global__ void __launch_bounds__(256) window_sum_tile_kernel(ConvArgs a, int32_
     }
 }
 
-// Plan preparation: pack w[K][R*S][C] into [Kpad][Jpad] with each tap's
-// channels padded from C to C4 (zeros in the extra channels, the K-tail and
-// the extra rows), and fold bias, term 2 and term 4 into chan[k].bconst.
-// The other chan fields and zpw were uploaded by the host; krec (or nullptr)
-// gets the channel's KRec.  One workgroup per (padded) output channel.
-__global__ void __launch_bounds__(256) prep_conv_kernel(const int8_t *w, const int32_t *bias, int K, int RS,
-                                                        int C, int C4, int Jpad, int32_t zpx, int8_t *wp,
-                                                        ChanRec *chan, const int32_t *zpw, KRec *krec)
+// Border class of four output pixels (see BorderTables).
+__device__ __forceinline__ void border_map(const BorderTables &b, unsigned quad)
 {
+    const unsigned m0 = quad * 4u;
+    if (m0 >= b.M)
+        return;
+    const unsigned t = m0 / (unsigned)b.Wo;
+    int ow = (int)(m0 - t * (unsigned)b.Wo), oh = (int)(t % (unsigned)b.Ho);
+    uint32_t v = 0;
+    for (int e = 0; e < 4; ++e) {
+        v |= (uint32_t)b.id[(int)b.rows[oh] * b.ncol + b.cols[ow]] << (8 * e);
+        if (++ow == b.Wo) {
+            ow = 0;
+            if (++oh == b.Ho)
+                oh = 0;
+        }
+    }
+    b.pcls[quad] = v;
+}
+
+// Corrections of one channel from its packed row, by a workgroup: 16 lanes sum
+// a tap's Cs bytes, then a thread adds up a class's taps.  The result wraps to
+// int32 like every other term of the accumulator, which is exact whenever the
+// final sum fits.
+__device__ __forceinline__ void border_corr(const BorderTables &b, const int8_t *row, int k, int Kpad, int Cs, int RS)
+{
+    __shared__ int tap[256];   // filters of at most 16 x 16
+    const int lane = (int)threadIdx.x & 15;
+    for (int t = (int)threadIdx.x >> 4; t < RS; t += 16) {
+        int sum = 0;
+        for (int c = lane * 4; c < Cs; c += 64)
+            sum = __builtin_amdgcn_sdot4(*(const int *)(row + (size_t)t * Cs + c), 0x01010101, sum, false);
+        for (int o = 1; o < 16; o <<= 1)
+            sum += __shfl_xor(sum, o);
+        if (lane == 0)
+            tap[t] = sum;
+    }
+    __syncthreads();
+    for (int cls = (int)threadIdx.x; cls < b.ncls; cls += 256) {
+        const uint32_t rm = b.rmask[cls], cm = b.cmask[cls];
+        int sum = 0;
+        for (int t = 0, r = 0, s = 0; t < RS; ++t) {
+            if (((rm >> r) & (cm >> s) & 1u) == 0)
+                sum += tap[t];
+            if (++s == b.S) {
+                s = 0;
+                ++r;
+            }
+        }
+        b.corr[(size_t)cls * Kpad + k] = (int32_t)((uint32_t)sum * (uint32_t)b.zpx);
+    }
+}
+
+// Plan preparation: pack w[K][R*S][C] into wp[Kpad][Jpad] (or nullptr: no
+// packing) with each tap's channels padded from C to Cs (zeros in the extra
+// channels, the K-tail and the extra rows), and fold bias, term 2 and term 4
+// (over the C4 channels of x) into chan[k].bconst.  The other chan fields and
+// zpw were uploaded by the host; krec (or nullptr) gets the channel's KRec.
+// One workgroup per (padded) output channel, and after those one per 1024
+// output pixels for the border classes: one launch, since a one-shot call is
+// bound by the number of them (a launch each for the classes and, one thread
+// per class and channel walking the bytes, the corrections: a creation of 32
+// 3x3 filters for 32x160x160x36 took 425 us, 60 unpadded; 512 filters of 512
+// channels 440 us, 150 of them the corrections; 71 and 120 us now).
+__global__ void __launch_bounds__(256) prep_conv_kernel(const int8_t *w, const int32_t *bias, int K, int RS,
+                                                        int C, int C4, int Cs, int Jpad, int Kpad, int32_t zpx,
+                                                        int8_t *wp, ChanRec *chan, const int32_t *zpw, KRec *krec,
+                                                        BorderTables border)
+{
+    if ((int)blockIdx.x >= Kpad) {
+        border_map(border, (blockIdx.x - (unsigned)Kpad) * 256u + threadIdx.x);
+        return;
+    }
     const int k = blockIdx.x;
     __shared__ long long part[256];
     long long sum = 0;
     for (int j = threadIdx.x; j < Jpad; j += blockDim.x) {
-        const int tap = j / C4, c = j - tap * C4;
+        const int tap = j / Cs, c = j - tap * Cs;
         int8_t v = 0;
         if (k < K && tap < RS && c < C)
             v = w[((size_t)k * RS + tap) * C + c];
-        wp[(size_t)k * Jpad + j] = v;
+        if (wp)
+            wp[(size_t)k * Jpad + j] = v;
         sum += v;
     }
     part[threadIdx.x] = sum;
@@ -704,6 +769,8 @@ __global__ void __launch_bounds__(256) prep_conv_kernel(const int8_t *w, const i
                                        ((unsigned long long)(uint32_t)chan[k].rndzp << 32)),
                            chan[k].mult, chan[k].shift - 32};
     }
+    if (border.ncls)   // the row was written by this workgroup before the barriers above
+        border_corr(border, wp + (size_t)k * Jpad, k, Kpad, Cs, RS);
 }
 
 // Depth of the register prefetch ring (stages in flight): 4 where the
@@ -826,12 +893,15 @@ hipError_t launch_window_sums(const ConvArgs &a, int32_t *out, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_prep_conv(const int8_t *w, const int32_t *bias, int K, int RS, int C, int C4, int Jpad,
+hipError_t launch_prep_conv(const int8_t *w, const int32_t *bias, int K, int RS, int C, int C4, int Cs, int Jpad,
                             int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, KRec *krec,
-                            hipStream_t st)
+                            const BorderTables &border, hipStream_t st)
 {
-    hipLaunchKernelGGL(prep_conv_kernel, dim3(Kpad), dim3(256), 0, st, w, bias, K, RS, C, C4, Jpad, zpx, wp,
-                       chan, zpw, krec);
+    if (border.ncls && (!wp || RS > 256 || Cs % 4 != 0 || Jpad % 4 != 0))
+        return hipErrorInvalidValue;
+    const unsigned map_blocks = border.ncls ? border.M / 1024u + (border.M % 1024u != 0) : 0u;
+    hipLaunchKernelGGL(prep_conv_kernel, dim3((unsigned)Kpad + map_blocks), dim3(256), 0, st, w, bias, K, RS, C, C4,
+                       Cs, Jpad, Kpad, zpx, wp, chan, zpw, krec, border);
     return hipGetLastError();
 }
 

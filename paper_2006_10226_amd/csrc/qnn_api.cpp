@@ -762,59 +762,59 @@ void tune_record(const std::string &key, const ConvKernel &k)
 // (row mask, column mask) pair with an outside tap is a class; pixels with
 // every tap inside get 255.
 struct BorderClasses {
-    std::vector<uint8_t> pcls;           // [M]
     std::vector<uint32_t> rmask, cmask;  // per class
+    // class of output pixel (oh, ow): id[rows[oh] * ncol + cols[ow]]
+    std::vector<uint8_t> rows, cols, id;
+    int ncol = 0;
     bool any = false;
 };
 
-bool border_classes(const ConvDesc &d, int Ho, int Wo, int64_t M, BorderClasses &bc)
+bool border_classes(const ConvDesc &d, int Ho, int Wo, BorderClasses &bc)
 {
     const uint32_t full_r = (1u << d.R) - 1, full_c = (1u << d.S) - 1;
+    // distinct masks u of the n coordinates of one direction, and each one's
+    auto masks = [](int n, int taps, int stride, int pad, int dil, int size, std::vector<uint32_t> &u,
+                    std::vector<uint8_t> &cls) {
+        cls.resize(n);
+        for (int o = 0; o < n; ++o) {
+            uint32_t m = 0;
+            for (int t = 0; t < taps; ++t) {
+                const int64_t i = (int64_t)o * stride - pad + (int64_t)t * dil;
+                m |= (uint32_t)(i >= 0 && i < size) << t;
+            }
+            // neighbours mostly share their mask: the latest first
+            const size_t q = std::find(u.rbegin(), u.rend(), m) - u.rbegin();
+            if (q == u.size()) {
+                if (u.size() == 255)
+                    return false;
+                u.push_back(m);
+                cls[o] = (uint8_t)(u.size() - 1);
+            } else {
+                cls[o] = (uint8_t)(u.size() - 1 - q);
+            }
+        }
+        return true;
+    };
     std::vector<uint32_t> ru, cu;
-    std::vector<int> rcls(Ho), ccls(Wo);
-    for (int oh = 0; oh < Ho; ++oh) {
-        uint32_t m = 0;
-        for (int r = 0; r < d.R; ++r) {
-            const int64_t ih = (int64_t)oh * d.cp.stride_h - d.cp.pad_top + (int64_t)r * d.cp.dil_h;
-            m |= (uint32_t)(ih >= 0 && ih < d.H) << r;
-        }
-        const auto it = std::find(ru.begin(), ru.end(), m);
-        rcls[oh] = (int)(it - ru.begin());
-        if (it == ru.end())
-            ru.push_back(m);
-    }
-    for (int ow = 0; ow < Wo; ++ow) {
-        uint32_t m = 0;
-        for (int s = 0; s < d.S; ++s) {
-            const int64_t iw = (int64_t)ow * d.cp.stride_w - d.cp.pad_left + (int64_t)s * d.cp.dil_w;
-            m |= (uint32_t)(iw >= 0 && iw < d.W) << s;
-        }
-        const auto it = std::find(cu.begin(), cu.end(), m);
-        ccls[ow] = (int)(it - cu.begin());
-        if (it == cu.end())
-            cu.push_back(m);
-    }
+    if (!masks(Ho, d.R, d.cp.stride_h, d.cp.pad_top, d.cp.dil_h, d.H, ru, bc.rows) ||
+        !masks(Wo, d.S, d.cp.stride_w, d.cp.pad_left, d.cp.dil_w, d.W, cu, bc.cols))
+        return false;
     const size_t ncls = ru.size() * cu.size();
     if (ncls > 255)
         return false;
+    bc.ncol = (int)cu.size();
     bc.rmask.resize(ncls);
     bc.cmask.resize(ncls);
-    std::vector<uint8_t> id(ncls);
+    bc.id.resize(ncls);
     for (size_t rc = 0; rc < ru.size(); ++rc)
         for (size_t cc = 0; cc < cu.size(); ++cc) {
             const size_t c = rc * cu.size() + cc;
             bc.rmask[c] = ru[rc];
             bc.cmask[c] = cu[cc];
             const bool interior = ru[rc] == full_r && cu[cc] == full_c;
-            id[c] = interior ? 255 : (uint8_t)c;
+            bc.id[c] = interior ? 255 : (uint8_t)c;
             bc.any |= !interior;
         }
-    bc.pcls.resize((size_t)M);
-    size_t m = 0;
-    for (int n = 0; n < d.N; ++n)
-        for (int oh = 0; oh < Ho; ++oh)
-            for (int ow = 0; ow < Wo; ++ow)
-                bc.pcls[m++] = id[(size_t)rcls[oh] * cu.size() + ccls[ow]];
     return true;
 }
 
@@ -1215,7 +1215,7 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     // the short-loop kernel takes every filter of at most 15 x 15 taps: where
     // a tap's channels do not fill 16-byte chunks, from weights packed that way
     const bool small_rs = d.R <= 15 && d.S <= 15;
-    const bool classes = (tap_ok || (small_rs && !rowpack)) && !linear && border_classes(d, Ho, Wo, M, bc);
+    const bool classes = (tap_ok || (small_rs && !rowpack)) && !linear && border_classes(d, Ho, Wo, bc);
     const bool dma_ok = tap_ok && (classes || linear);
     bool flow_ok = rowpack || linear || (small_rs && classes);
     const bool pcorr = classes && bc.any && zpx != 0;
@@ -1261,83 +1261,8 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     if (flow_ok)
         add_flow_candidates(cands, M, d.K, (int)((Jf + 63) / 64), linear, term3);
 
-    const size_t wp_bytes = align_up((size_t)Kpad * Jpad, 256);
-    // the same weights in MFMA operand order (of the short-loop kernel's packing where it has one of its own)
-    const size_t wf_bytes = dma_ok || flow_ok ? align_up((size_t)Kpad * fJpad, 256) : 0;
-    const size_t wq_bytes = flow_ok && own_pack ? align_up((size_t)Kpad * fJpad, 256) : 0;
-    const size_t wr_bytes = rowpack ? align_up((size_t)Kpad * Jr, 256) : 0;
-    const size_t ch_bytes = align_up(sizeof(ChanRec) * Kpad, 256);
-    const size_t kr_bytes = krec_ok ? ch_bytes : 0;
-    const size_t zw_bytes = align_up(sizeof(int32_t) * Kpad, 256);
-    const size_t pad_bytes = 256;
-    const size_t pcls_bytes = pcorr ? align_up((size_t)M, 256) : 0;
-    const size_t corr_bytes = pcorr ? align_up(sizeof(int32_t) * ncls * Kpad, 256) : 0;
-    const size_t mask_bytes = pcorr ? align_up(sizeof(uint32_t) * 2 * ncls, 256) : 0;
-    const size_t total =
-        wp_bytes + wf_bytes + wr_bytes + wq_bytes + ch_bytes + kr_bytes + zw_bytes + pad_bytes + pcls_bytes + corr_bytes +
-        mask_bytes;
-    hipError_t e = hipMalloc(&p->dev, total);
-    if (e != hipSuccess) {
-        free_plan(p);
-        return fail(QNN_ERR_ALLOC, "hipMalloc of %zu bytes failed", total);
-    }
-    int8_t *wp = (int8_t *)p->dev;
-    int8_t *wf = wf_bytes ? wp + wp_bytes : nullptr;
-    int8_t *wr = rowpack ? wp + wp_bytes + wf_bytes : nullptr;
-    int8_t *wq = wq_bytes ? wp + wp_bytes + wf_bytes + wr_bytes : nullptr;
-    KRec *krec = kr_bytes ? (KRec *)((char *)p->dev + wp_bytes + wf_bytes + wr_bytes + wq_bytes) : nullptr;
-    ChanRec *chan = (ChanRec *)((char *)p->dev + wp_bytes + wf_bytes + wr_bytes + wq_bytes + kr_bytes);
-    int32_t *zpw_d = (int32_t *)((char *)chan + ch_bytes);
-    uint8_t *padbuf = (uint8_t *)zpw_d + zw_bytes;
-    // channel records, weight zero points and the padding block (zp_x
-    // bytes) in one upload
-    std::vector<uint8_t> host(ch_bytes + zw_bytes + pad_bytes, 0);
-    for (int k = 0; k < Kpad; ++k) {
-        ChanRec r{0, 0, 0, 33};
-        int32_t z = 0;
-        if (k < d.K) {
-            r.mult = mult[k];
-            r.shift = shift[k];
-            if (fast) {
-                const int sh = shift[k] - 32;
-                r.rndzp = (int32_t)((1LL << (sh - 1)) + (int64_t)(zpy + off8) * (1LL << sh));
-            }
-            z = d.wq.zero_point[d.wq.n == 1 ? 0 : k];
-        }
-        std::memcpy(host.data() + sizeof(ChanRec) * k, &r, sizeof r);
-        std::memcpy(host.data() + ch_bytes + sizeof(int32_t) * k, &z, sizeof z);
-    }
-    std::memset(host.data() + ch_bytes + zw_bytes, (uint8_t)zpx, pad_bytes);
-    uint8_t *pcls_d = padbuf + pad_bytes;
-    int32_t *corr_d = (int32_t *)(pcls_d + pcls_bytes);
-    uint32_t *mask_d = (uint32_t *)((char *)corr_d + corr_bytes);
-    std::vector<uint32_t> masks;
-    if (pcorr) {
-        masks = bc.rmask;
-        masks.insert(masks.end(), bc.cmask.begin(), bc.cmask.end());
-    }
-    if ((e = hipMemcpyAsync(chan, host.data(), host.size(), hipMemcpyHostToDevice, st)) != hipSuccess ||
-        (e = launch_prep_conv(d.w, d.bias, d.K, RS, d.C, C4, Jpad, Kpad, zpx_l, wp, chan, zpw_d, krec, st)) !=
-            hipSuccess ||
-        (wr && (e = launch_rowpack_weights(d.w, d.K, d.R, d.S, d.C, C4, Kpad, Jr, wr, st)) != hipSuccess) ||
-        (wq && (e = launch_tap_pack(d.w, d.K, RS, d.C, C16, Kpad, (int)fJpad, wq, st)) != hipSuccess) ||
-        (wf && (e = launch_frag_pack(wr ? wr : wq ? wq : wp, Kpad, (int)fJpad, wf, st)) != hipSuccess) ||
-        (pcorr && ((e = hipMemcpyAsync(pcls_d, bc.pcls.data(), (size_t)M, hipMemcpyHostToDevice, st)) != hipSuccess ||
-                   (e = hipMemcpyAsync(mask_d, masks.data(), sizeof(uint32_t) * masks.size(), hipMemcpyHostToDevice,
-                                       st)) != hipSuccess ||
-                   (e = launch_border_corr(wp, Kpad, Jpad, C4, d.S, RS, mask_d, mask_d + ncls, (int)ncls, zpx, corr_d,
-                                           st)) != hipSuccess)) ||
-        (e = hipStreamSynchronize(st)) != hipSuccess) {
-        free_plan(p);
-        return hip_fail(e, "conv plan preparation");
-    }
-
+    // ---- the call's geometry and options
     ConvArgs &a = p->conv;
-    a.wp = wp;
-    a.wf = wf;
-    a.chan = chan;
-    a.zpw = zpw_d;
-    a.padbuf = padbuf;
     a.N = d.N; a.H = d.H; a.W = d.W; a.C = C4; a.Ho = Ho; a.Wo = Wo; a.R = d.R; a.S = d.S;
     a.sh = d.cp.stride_h; a.sw = d.cp.stride_w; a.pt = d.cp.pad_top; a.pl = d.cp.pad_left;
     a.dh = d.cp.dil_h; a.dw = d.cp.dil_w;
@@ -1361,12 +1286,9 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     a.lo_off = lo + off8;
     a.hi_off = hi + off8;
     a.out_xor = off8 ? 0x80808080u : 0u;
-    a.krec = krec;
     a.sat_pack = a.lo_off <= 0 && a.hi_off >= 255;
     a.staged = staged;
     a.zp4 = 0x01010101u * (uint32_t)(uint8_t)zpx_l;
-    const int32_t *pcorr_tab = pcorr ? corr_d : nullptr;
-    const uint8_t *pcls_tab = pcorr ? pcls_d : nullptr;
     a.chan_in_lds = (size_t)Kpad * sizeof(ChanRec) <= 64 * 1024;
     make_divider((uint32_t)Wo, a.mWo, a.sWo);
     make_divider((uint32_t)Ho, a.mHo, a.sHo);
@@ -1378,7 +1300,6 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     p->H_in = d.H; p->W_in = d.W; p->pt_in = d.cp.pad_top; p->pl_in = d.cp.pad_left;
     if (rowpack) {
         // the kernel sees the padded image, unpadded, with row pairs as taps
-        a.wp = wr;
         a.Jpad = Jr;
         a.J = Jr;
         a.H = Hp; a.W = Wp;
@@ -1387,7 +1308,6 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
         a.rowpack = 1;
         a.row_bytes = Wp * C4;
     }
-    a.fw = rowpack ? wr : wq ? wq : wp;
     a.fJpad = (int)fJpad;
     a.fJ = (int)Jf;
     a.linear = linear;
@@ -1447,6 +1367,8 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
     if (timed.empty())
         timed = cands;
     ConvKernel best = timed[0];
+    const std::string key = tune_key(d, term3, ncls, fast);
+    bool tune_now = false;
     if (timed.size() > 1) {
         if (timed[0].fam == FAM_FLOW || timed[0].fam == FAM_SMALL)
             best = default_kernel(timed, M, d.K, (int)((Jf + 63) / 64));
@@ -1456,17 +1378,115 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
                 fusable.push_back(k);
         if (!fusable.empty())
             p->fuse_ker = default_kernel(fusable, M, d.K, (int)((Jf + 63) / 64));
-        if (M > 0 && env_int("QNN_AUTOTUNE", 1) != 0) {
-            const std::string key = tune_key(d, term3, ncls, fast);
-            if (!tune_lookup(key, cands, &best) && tune) {
-                if ((s = autotune_conv(a, timed, p->avec, term3, pcorr_tab, pcls_tab, st, &best,
-                                       &p->fuse_ker)) != QNN_OK) {
-                    free_plan(p);
-                    return s;
-                }
-                tune_record(key, best);
+        if (M > 0 && env_int("QNN_AUTOTUNE", 1) != 0)
+            tune_now = !tune_lookup(key, cands, &best) && tune;
+    }
+
+    // ---- device tables: those that the kernels to be timed, or the chosen
+    // one, read and no others (a one-shot call pays for all of it each time)
+    auto uses = [&](std::initializer_list<int> fams) {
+        for (const ConvKernel &k : tune_now ? timed : std::vector<ConvKernel>{best})
+            if (std::find(fams.begin(), fams.end(), k.fam) != fams.end())
+                return true;
+        return false;
+    };
+    // (either all of them are short-loop and few-pixel kernels or none is)
+    const bool tap_pack = own_pack && uses({FAM_FLOW, FAM_SMALL});
+    const int pack_C = tap_pack ? C16 : C4, pack_J = tap_pack ? (int)fJpad : Jpad;
+    const bool zero_pad = uses({FAM_DMA, FAM_WAVE, FAM_FLOW, FAM_SMALL});
+    const bool corr = pcorr && zero_pad && M > 0;
+    const size_t wp_bytes = rowpack ? align_up((size_t)Kpad * Jr, 256) : align_up((size_t)Kpad * pack_J, 256);
+    // the same weights in MFMA operand order
+    const size_t wf_bytes = uses({FAM_SMALL, FAM_WAVE, FAM_HALO, FAM_WIN}) ? wp_bytes : 0;
+    const size_t kr_bytes = krec_ok && uses({FAM_FLOW}) ? align_up(sizeof(KRec) * Kpad, 256) : 0;
+    const size_t pcls_bytes = corr ? align_up((size_t)M, 256) : 0;
+    const size_t corr_bytes = corr ? align_up(sizeof(int32_t) * ncls * Kpad, 256) : 0;
+    // uploaded in one piece: channel records, weight zero points, the padding
+    // block (zp_x bytes), the border classes
+    const size_t ch_bytes = align_up(sizeof(ChanRec) * Kpad, 256);
+    const size_t zw_bytes = align_up(sizeof(int32_t) * Kpad, 256);
+    const size_t pad_bytes = 256;
+    const size_t mask_bytes = corr ? align_up(sizeof(uint32_t) * 2 * ncls, 256) : 0;
+    const size_t cls_bytes = corr ? align_up((size_t)Ho + Wo + ncls, 256) : 0;
+    const size_t up_bytes = ch_bytes + zw_bytes + pad_bytes + mask_bytes + cls_bytes;
+    const size_t total = wp_bytes + wf_bytes + kr_bytes + pcls_bytes + corr_bytes + up_bytes;
+    hipError_t e = hipMalloc(&p->dev, total);
+    if (e != hipSuccess) {
+        free_plan(p);
+        return fail(QNN_ERR_ALLOC, "hipMalloc of %zu bytes failed", total);
+    }
+    char *next = (char *)p->dev;
+    auto take = [&](size_t bytes) {
+        char *q = bytes ? next : nullptr;
+        next += bytes;
+        return q;
+    };
+    int8_t *wp = (int8_t *)take(wp_bytes);
+    int8_t *wf = (int8_t *)take(wf_bytes);
+    KRec *krec = (KRec *)take(kr_bytes);
+    uint8_t *pcls_d = (uint8_t *)take(pcls_bytes);
+    int32_t *corr_d = (int32_t *)take(corr_bytes);
+    ChanRec *chan = (ChanRec *)take(ch_bytes);
+    int32_t *zpw_d = (int32_t *)take(zw_bytes);
+    uint8_t *padbuf = (uint8_t *)take(pad_bytes);
+    uint32_t *mask_d = (uint32_t *)take(mask_bytes);
+    uint8_t *cls_d = (uint8_t *)take(cls_bytes);
+    std::vector<uint8_t> host(up_bytes, 0);
+    for (int k = 0; k < Kpad; ++k) {
+        ChanRec r{0, 0, 0, 33};
+        int32_t z = 0;
+        if (k < d.K) {
+            r.mult = mult[k];
+            r.shift = shift[k];
+            if (fast) {
+                const int sh = shift[k] - 32;
+                r.rndzp = (int32_t)((1LL << (sh - 1)) + (int64_t)(zpy + off8) * (1LL << sh));
             }
+            z = d.wq.zero_point[d.wq.n == 1 ? 0 : k];
         }
+        std::memcpy(host.data() + sizeof(ChanRec) * k, &r, sizeof r);
+        std::memcpy(host.data() + ch_bytes + sizeof(int32_t) * k, &z, sizeof z);
+    }
+    std::memset(host.data() + ch_bytes + zw_bytes, (uint8_t)zpx, pad_bytes);
+    if (corr) {
+        uint8_t *h = host.data() + ch_bytes + zw_bytes + pad_bytes;
+        std::memcpy(h, bc.rmask.data(), sizeof(uint32_t) * ncls);
+        std::memcpy(h + sizeof(uint32_t) * ncls, bc.cmask.data(), sizeof(uint32_t) * ncls);
+        h += mask_bytes;
+        std::memcpy(h, bc.rows.data(), Ho);
+        std::memcpy(h + Ho, bc.cols.data(), Wo);
+        std::memcpy(h + Ho + Wo, bc.id.data(), ncls);
+    }
+    BorderTables border{};
+    if (corr)
+        border = BorderTables{cls_d, cls_d + Ho, cls_d + Ho + Wo, mask_d, mask_d + ncls, (int)ncls, bc.ncol,
+                              Ho, Wo, d.S, (unsigned)M, zpx, (uint32_t *)pcls_d, corr_d};
+    if ((e = hipMemcpyAsync(chan, host.data(), host.size(), hipMemcpyHostToDevice, st)) != hipSuccess ||
+        (e = launch_prep_conv(d.w, d.bias, d.K, RS, d.C, C4, pack_C, pack_J, Kpad, zpx_l, rowpack ? nullptr : wp, chan,
+                              zpw_d, krec, border, st)) != hipSuccess ||
+        (rowpack &&
+         (e = launch_rowpack_weights(d.w, d.K, d.R, d.S, d.C, C4, Kpad, Jr, wp, st)) != hipSuccess) ||
+        (wf && (e = launch_frag_pack(wp, Kpad, rowpack ? Jr : pack_J, wf, st)) != hipSuccess) ||
+        (e = hipStreamSynchronize(st)) != hipSuccess) {
+        free_plan(p);
+        return hip_fail(e, "conv plan preparation");
+    }
+    a.wp = wp;
+    a.fw = wp;
+    a.wf = wf;
+    a.chan = chan;
+    a.krec = krec;
+    a.zpw = zpw_d;
+    a.padbuf = padbuf;
+    const int32_t *pcorr_tab = corr ? corr_d : nullptr;
+    const uint8_t *pcls_tab = corr ? pcls_d : nullptr;
+
+    if (tune_now) {
+        if ((s = autotune_conv(a, timed, p->avec, term3, pcorr_tab, pcls_tab, st, &best, &p->fuse_ker)) != QNN_OK) {
+            free_plan(p);
+            return s;
+        }
+        tune_record(key, best);
     }
     p->ker = best;
     set_tiling(a, best, p->avec, pcorr_tab, pcls_tab);

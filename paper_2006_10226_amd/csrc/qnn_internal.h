@@ -449,8 +449,6 @@ enum SmallTile {
 TileShape small_tile_shape(int tile);
 size_t small_lds_bytes(int tile, int nk, bool linear);
 hipError_t launch_conv_small(const ConvArgs &a, int tile, hipStream_t st);
-hipError_t launch_tap_pack(const int8_t *w, int K, int RS, int C, int C16, int Kpad, int Jpad, int8_t *out,
-                           hipStream_t st);
 
 TileShape dma_tile_shape(int tile);
 int dma_threads(int tile);
@@ -487,15 +485,15 @@ size_t win_lds_bytes(const ConvArgs &a, int cfg);               // 0: not eligib
 long long win_workgroups_per_ctile(const ConvArgs &a, int cfg);  // -1: not eligible
 hipError_t launch_conv_window(const ConvArgs &a, int cfg, hipStream_t st);
 hipError_t launch_frag_pack(const int8_t *wp, int Kpad, int Jpad, int8_t *out, hipStream_t st);
-// corr[c][k] = zp_x * (sum of packed weights of row k over the taps outside
-// the image in border class c: tap (r, s) is inside when bit r of rmask[c]
-// and bit s of cmask[c] are set).
 hipError_t launch_rowpack_weights(const int8_t *w, int K, int R, int S, int C, int C4, int Kpad, int Jpad, int8_t *wp,
                                   hipStream_t st);
 hipError_t launch_pad_image(const uint8_t *x, int N, int H, int W, int C, int Hp, int Wp, int C4, int pt, int pl,
                             uint8_t zp, uint8_t *out, hipStream_t st);
-hipError_t launch_border_corr(const int8_t *wp, int Kpad, int Jpad, int C4, int S, int RS, const uint32_t *rmask,
+hipError_t launch_border_corr(const int8_t *wp, int Kpad, int Jpad, int Cs, int S, int RS, const uint32_t *rmask,
                               const uint32_t *cmask, int ncls, int32_t zpx, int32_t *corr, hipStream_t st);
+// pcls[m] = id[rows[oh] * ncol + cols[ow]] of every output pixel m.
+hipError_t launch_border_map(const uint8_t *rows, const uint8_t *cols, const uint8_t *id, int ncol, int Ho, int Wo,
+                             long long M, uint8_t *pcls, hipStream_t st);
 int tap_threads(int tile);
 int tap_wave_tile(int tile);   // channels x pixels of one wave
 hipError_t launch_conv_tap(const ConvArgs &a, int tile, hipStream_t st);
@@ -511,8 +509,23 @@ int conv_blocks_per_cu(int tile, int avec, size_t dyn_lds);
 hipError_t launch_window_sums(const ConvArgs &a, int32_t *out, hipStream_t st);
 hipError_t launch_pad_channels(const uint8_t *x, uint8_t *xp, long long pixels, int C, int C4, uint8_t zp,
                                hipStream_t st);
-hipError_t launch_prep_conv(const int8_t *w, const int32_t *bias, int K, int RS, int C, int C4, int Jpad,
-                            int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, KRec *krec, hipStream_t st);
+// Border tables of a padded conv, filled by the same launch (ncls == 0: none):
+// pcls[m] = id[rows[oh] * ncol + cols[ow]] of every output pixel m (pcls a
+// multiple of 4 bytes), and corr[c][k] = zp_x * (sum of row k's packed weights
+// over the taps outside the image in border class c: tap (r, s) is inside when
+// bit r of rmask[c] and bit s of cmask[c] are set).
+struct BorderTables {
+    const uint8_t *rows, *cols, *id;
+    const uint32_t *rmask, *cmask;
+    int ncls, ncol, Ho, Wo, S;
+    unsigned M;
+    int32_t zpx;
+    uint32_t *pcls;
+    int32_t *corr;
+};
+hipError_t launch_prep_conv(const int8_t *w, const int32_t *bias, int K, int RS, int C, int C4, int Cs, int Jpad,
+                            int Kpad, int32_t zpx, int8_t *wp, ChanRec *chan, const int32_t *zpw, KRec *krec,
+                            const BorderTables &border, hipStream_t st);
 hipError_t launch_prep_dw(const int8_t *w, const int32_t *bias, int RS, int C, const int32_t *zpw, int32_t *wq,
                           ChanRec *chan, hipStream_t st);
 hipError_t launch_depthwise(const DwArgs &a, hipStream_t st);
