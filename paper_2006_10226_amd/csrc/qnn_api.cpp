@@ -2248,7 +2248,7 @@ qnn_status qnn_plan_set_residual(qnn_plan *plan, qnn_dtype r_dtype, qnn_qparams 
     plan->conv.r_coff = r_coff;
     plan->conv.rdt = r_dtype == QNN_INT8 ? 1 : 0;
     plan->fused = true;
-    plan->desc += args.tab || args.flt ? " +add" : " +add(no-tables)";
+    plan->desc += args.flt ? " +add(f32)" : args.tab ? " +add" : " +add(no-tables)";
     return QNN_OK;
 }
 

@@ -2,8 +2,9 @@
 qnn_plan_run_residual): byte-exact against the oracle's conv followed by
 the oracle's qnn.add, for the kernel families that have the fused epilogue,
 every dtype combination of the intermediate, the residual and the sum, both
-rounding forms of the add, residual and output channel slices (16-byte and
-byte paths), and the plans that must refuse it."""
+rounding forms of the add, the add's forms (f32 terms, term tables, 64-bit),
+residual and output channel slices (16-byte and byte paths), and the plans
+that must refuse it."""
 import numpy as np
 import pytest
 import torch
@@ -23,6 +24,10 @@ SHAPES = [
 ]
 
 
+# the add's form as a plan describes it: f32 terms, or (QNN_FLOAT_ADD=0) term tables
+FORMS = [pytest.param({}, " +add(f32)", id="f32"), pytest.param(dict(QNN_FLOAT_ADD=0), " +add", id="tables")]
+
+
 def _residual(shape, dtype, seed, r_ldc=None, r_coff=0):
     rng = np.random.default_rng(seed)
     N, Ho, Wo, K = shape
@@ -36,7 +41,8 @@ def _residual(shape, dtype, seed, r_ldc=None, r_coff=0):
 
 @pytest.mark.parametrize("i", range(len(SHAPES)))
 @pytest.mark.parametrize("dts", [("u8", "u8", "u8"), ("i8", "i8", "i8"), ("u8", "i8", "i8"), ("i8", "u8", "u8")])
-def test_fused_add_matches_conv_then_add(i, dts):
+@pytest.mark.parametrize("form,suffix", FORMS)
+def test_fused_add_matches_conv_then_add(i, dts, form, suffix):
     layer, N, forced = SHAPES[i]
     yt, rt, ot = dts
     c = W.conv_case(layer, N, seed=900 + i, yt=yt)
@@ -50,8 +56,10 @@ def test_fused_add_matches_conv_then_add(i, dts):
         with env(**forced):
             p, keep = make_plan(c, y_ldc=y_ldc)
         d = p.describe()
-        assert d.startswith(("conv_dma", "conv_tap")), d
-        p.set_residual(rt, s_r, zp_r, s_o, zp_o, ot, act=act, rounding=rounding)
+        assert d.startswith(("conv_dma tile", "conv_tap")), d
+        with env(**form):
+            p.set_residual(rt, s_r, zp_r, s_o, zp_o, ot, act=act, rounding=rounding)
+        assert p.describe().endswith(suffix), p.describe()
         y = p.run(dev(c.x), residual=dev(full))
         torch.cuda.synchronize()
         log(f"fused add {layer.name} {dts} {rounding}: {p.describe()}")
@@ -60,10 +68,10 @@ def test_fused_add_matches_conv_then_add(i, dts):
 
 
 def test_fused_add_term_tables_and_without():
-    """The epilogue adds through the plan's per-byte term tables wherever a
-    32-bit sum of two terms cannot overflow, and through the add's own
-    64-bit arithmetic where it can (a residual scale 10^7 times the
-    output's); both byte-exact."""
+    """Where the f32 terms are left out, the epilogue adds through the plan's
+    per-byte term tables wherever a 32-bit sum of two terms cannot overflow,
+    and through the add's own 64-bit arithmetic where it can (a residual
+    scale 10^7 times the output's); both byte-exact."""
     layer = W.ConvLayer("t1x1", 6, 9, 64, 64, 1, 1, 1, (0, 0, 0, 0))
     c = W.conv_case(layer, 2, seed=31)
     mid = run_oracle(c)
@@ -71,9 +79,9 @@ def test_fused_add_term_tables_and_without():
                                          (0.0004096, 4096.0, 250, 7, True)):
         full, r = _residual(mid.shape, "u8", seed=9)
         ref = O.add(mid, c.s_y, c.zp_y, r, s_r, zp_r, s_o, zp_o, "u8", None)
-        with env(QNN_DMA=15):
+        with env(QNN_DMA=15, QNN_FLOAT_ADD=0):
             p, keep = make_plan(c)
-        p.set_residual("u8", s_r, zp_r, s_o, zp_o, "u8")
+            p.set_residual("u8", s_r, zp_r, s_o, zp_o, "u8")
         d = p.describe()
         assert d.endswith(" +add") == tables and d.endswith("+add(no-tables)") != tables, d
         y = p.run(dev(c.x), residual=dev(full))
@@ -154,16 +162,20 @@ DMA_SHORT = {t: s for t, s in zip(range(15, 26), [1, 1, 1, 1, 2, 2, 2, 2, 4, 4, 
 TAP_FUSED = list(range(8))
 
 
-def _fused_case(layer, N, seed, env_kw, what, **kw):
+def _fused_case(layer, N, seed, env_kw, suffix, what, **kw):
+    # 0.041 / 0.05 has ties, whose terms no f32 multiply-add gives; 0.0417 / 0.05 has none
+    s_r = 0.0417 if "f32" in suffix else 0.041
     c = W.conv_case(layer, N, seed=seed, **kw)
     mid = run_oracle(c)
     full, r = _residual(mid.shape, "i8", seed=seed + 1)
-    ref = O.add(mid, c.s_y, c.zp_y, r, 0.041, -9, 0.05, 3 if c.yt == "i8" else 110, c.yt, None)
+    ref = O.add(mid, c.s_y, c.zp_y, r, s_r, -9, 0.05, 3 if c.yt == "i8" else 110, c.yt, None)
     y_ldc = -(-layer.Cout // 16) * 16
     with env(**env_kw):
         p, keep = make_plan(c, y_ldc=y_ldc)
+    with env(**env_kw):
+        p.set_residual("i8", s_r, -9, 0.05, 3 if c.yt == "i8" else 110, c.yt)
     d = p.describe()
-    p.set_residual("i8", 0.041, -9, 0.05, 3 if c.yt == "i8" else 110, c.yt)
+    assert d.endswith(suffix), d
     with env(**env_kw):
         y = p.run(dev(c.x), residual=dev(full))
     torch.cuda.synchronize()
@@ -174,7 +186,8 @@ def _fused_case(layer, N, seed, env_kw, what, **kw):
 
 
 @pytest.mark.parametrize("tile", DMA_FUSED)
-def test_fused_add_every_dma_tile(tile):
+@pytest.mark.parametrize("form,suffix", FORMS)
+def test_fused_add_every_dma_tile(tile, form, suffix):
     """Every LDS-direct configuration that has the fused epilogue: a 1x1
     conv within its short form's K-steps (or a 3x3 conv with padding,
     int8 input and weight zero points for the ring forms), ragged channels
@@ -185,14 +198,16 @@ def test_fused_add_every_dma_tile(tile):
     else:
         layer = W.ConvLayer("f3", 10, 9, 64, 136, 3, 3, 1, (1, 1, 1, 1))
         kw = dict(x_dtype="i8", zp_w="channel", yt="i8")
-    d = _fused_case(layer, 3, 500 + tile, dict(QNN_DMA=tile), f"dma {tile}", **kw)
-    assert d.startswith("conv_dma"), d
+    d = _fused_case(layer, 3, 500 + tile, dict(QNN_DMA=tile, **form), suffix, f"dma {tile}", **kw)
+    assert d.startswith("conv_dma tile"), d
 
 
 @pytest.mark.parametrize("tile", TAP_FUSED)
-def test_fused_add_every_tap_tile(tile):
+@pytest.mark.parametrize("form,suffix", FORMS)
+def test_fused_add_every_tap_tile(tile, form, suffix):
     layer = W.ConvLayer("t3", 11, 10, 128, 100, 3, 3, 1, (1, 1, 1, 1))
-    d = _fused_case(layer, 2, 600 + tile, dict(QNN_TAP=tile), f"tap {tile}", yt="i8")
+    d = _fused_case(layer, 2, 600 + tile, dict(QNN_TAP=tile, **form), suffix, f"tap {tile}",
+                    yt="i8")
     assert d.startswith("conv_tap"), d
 
 
