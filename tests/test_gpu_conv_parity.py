@@ -189,10 +189,9 @@ VARIANTS = [
     ("dw_5x5_i32", W.ConvLayer("v", 9, 9, 16, 16, 5, 5, 1, (2, 2, 2, 2), depthwise=True), 2, dict(yt="i32")),
     ("dw_half_away", W.ConvLayer("v", 8, 8, 64, 64, 3, 3, 1, (1, 1, 1, 1), depthwise=True), 2,
      dict(rounding="half_away")),
-    # the two-stage rounding through every epilogue: the LDS-direct / tap
-    # kernels (3x3, C % 64 == 0), the short 1x1 form, the gather kernel (C
-    # not a multiple of 64), the dot-product depthwise kernel and the
-    # general one, int8 and uint8 outputs
+    # the two-stage rounding through every epilogue: the kernel of the plan's
+    # own choice and those of FORCED, the dot-product depthwise kernel and
+    # the general one, int8 and uint8 outputs
     ("two_stage", W.ConvLayer("v", 10, 10, 64, 64, 3, 3, 1, (1, 1, 1, 1)), 2, dict(rounding="two_stage")),
     ("two_stage_1x1_i8", W.ConvLayer("v", 9, 9, 256, 100, 1, 1), 3, dict(rounding="two_stage", yt="i8")),
     ("two_stage_gather", W.ConvLayer("v", 9, 9, 20, 36, 3, 3, 1, (1, 1, 1, 1)), 2, dict(rounding="two_stage")),
@@ -204,11 +203,31 @@ VARIANTS = [
 ]
 
 
+# kernels that a variant also runs on (knob, describe prefix)
+FORCED = {
+    "two_stage": [("QNN_DMA=0", "conv_dma tile"), ("QNN_TAP=0", "conv_tap"), ("QNN_HALO=8", "conv_halo"),
+                  ("QNN_WIN=0", "conv_window")],
+    "two_stage_1x1_i8": [("QNN_DMA=23", "conv_dma tile"), ("QNN_TAP=0", "conv_tap")],
+    "two_stage_gather": [("QNN_TILE=3", "conv_mfma")],
+    "two_stage_deep": [("QNN_DMA=4", "conv_dma tile"), ("QNN_WAVE=2", "conv_wave")],
+}
+
+
 @pytest.mark.parametrize("name,layer,N,kw", VARIANTS, ids=[v[0] for v in VARIANTS])
 def test_conv_variants(name, layer, N, kw):
     c = W.conv_case(layer, N, seed=zlib.crc32(name.encode()) % 1000, **kw)
     log(f"variant {name}")
-    assert_equal(run_gpu(c), run_oracle(c), name)
+    ref = run_oracle(c)
+    assert_equal(run_gpu(c), ref, name)
+    for knob, prefix in FORCED.get(name, []):
+        with env(**dict([knob.split("=")])):
+            p, keep = make_plan(c)
+        d = p.describe()
+        assert d.startswith(prefix), d
+        y = p.run(dev(c.x)).cpu().numpy()
+        p.close()
+        log(f"variant {name} {knob}: {d}")
+        assert_equal(y, ref, f"{name} {knob}")
 
 
 @pytest.mark.parametrize("tile", list(range(9)))
@@ -373,7 +392,7 @@ def test_every_dma_tile(tile):
         for i, (layer, N, kw) in enumerate(shapes):
             c = W.conv_case(layer, N, seed=100 + tile * 10 + i, **kw)
             p, keep = make_plan(c)
-            assert p.describe().startswith("conv_dma"), p.describe()
+            assert p.describe().startswith("conv_dma tile"), p.describe()
             p.close()
             log(f"dma tile {tile} shape {i}")
             assert_equal(run_gpu(c), run_oracle(c), f"dma tile {tile} shape {i} {kw}")
@@ -413,7 +432,7 @@ def test_dma_channel_slice_output(layer, tile, coff):
     with env(QNN_DMA=tile):
         p, keep = make_plan(c, y_ldc=total, y_coff=coff)
         d = p.describe()
-        assert d.startswith("conv_dma"), d
+        assert d.startswith("conv_dma tile"), d
         out = torch.full((3, 12, 13, total), 77, dtype=torch.uint8, device="cuda")
         p.run(dev(c.x), out=out)
         torch.cuda.synchronize()
@@ -549,12 +568,13 @@ def test_every_tap_tile(tile):
             assert_equal(run_gpu(c), run_oracle(c), f"tap tile {tile} shape {i} {kw}")
 
 
-@pytest.mark.parametrize("C,forced", [(64, "dma"), (128, "tap"), (20, "gather"), (64, "auto")])
+@pytest.mark.parametrize("C,forced", [(64, "dma"), (128, "tap"), (20, "gather"), (64, "auto"), (20, "auto")])
 def test_dilation(C, forced):
     """Dilated taps (Eq. (2) with the tap index scaled by the dilation)."""
     layer = W.ConvLayer("dil", 15, 13, C, 40, 3, 3, 1, (2, 1, 2, 3))
     c = W.conv_case(layer, 2, seed=C)
-    cfg = {"dma": dict(QNN_DMA=0), "tap": dict(QNN_TAP=3), "gather": {}, "auto": {}}[forced]
+    cfg, prefix = {"dma": (dict(QNN_DMA=0), "conv_dma tile"), "tap": (dict(QNN_TAP=3), "conv_tap"),
+                   "gather": (dict(QNN_TILE=3), "conv_mfma"), "auto": ({}, "conv_dma_")}[forced]
     w, b = dev(c.w), dev(c.bias)
     with env(**cfg):
         p = Q.conv2d_plan(c.x.shape, "u8", c.s_x, c.zp_x, w, c.s_w, c.zp_w, b, 1, c.pads, (2, 2), c.s_y, c.zp_y,
@@ -562,6 +582,7 @@ def test_dilation(C, forced):
     y = p.run(dev(c.x))
     torch.cuda.synchronize()
     log(f"dilation C={C} {forced}: {p.describe()}")
+    assert p.describe().startswith(prefix), p.describe()
     p.close()
     ref = O.conv2d(c.x, c.s_x, c.zp_x, c.w, c.s_w, c.zp_w, c.bias, c.s_y, c.zp_y, c.yt, c.act, c.rounding,
                    (1, 1), c.pads, (2, 2))
