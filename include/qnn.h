@@ -396,7 +396,9 @@ qnn_status qnn_time_next_kernel(void *start_event, void *stop_event);
  * leave the plan as it was.  r_ldc >= r_coff + K.  A fused plan runs only
  * through qnn_plan_run_residual.  A plan whose own choice is the largest
  * tile, which has no fused epilogue, turns to the fastest of its candidates
- * that has one (qnn_plan_describe changes with it).  Where an f32
+ * that has one, as timed or recorded with that choice (qnn_plan_describe
+ * changes with it); where neither is the case (a kernel-choice file that
+ * names the largest tile only), to the one that the tile counts favour.  Where an f32
  * multiply-add gives every per-byte term of the add exactly, nothing is
  * allocated; else, where the terms fit 32-bit sums, the call tabulates them
  * in a 2 KB device buffer that the plan owns

@@ -512,6 +512,47 @@ bool can_fuse(const ConvKernel &k)
     return wave_tile != 0 && wave_tile <= kFuseMaxWaveTile;
 }
 
+// "family tile=CxPxK threads=N stages=S" of a kernel other than the gather one
+// ("s" after the stages: a short form).
+std::string kernel_text(const ConvKernel &k)
+{
+    static const char *fam_name[] = {"conv_mfma", "conv_tap",    "conv_dma",      "conv_wave",
+                                     "conv_halo", "conv_window", "conv_dma_flow", "conv_dma_small"};
+    const TileShape ts = kernel_shape(k);
+    int threads = 0, stages = 2;
+    bool sh = false;
+    switch (k.fam) {
+    case FAM_DMA:
+        threads = dma_threads(k.tile);
+        stages = dma_stages(k.tile);
+        sh = dma_short(k.tile);
+        break;
+    case FAM_FLOW:
+        threads = flow_threads(k.tile);
+        stages = flow_stages(k.tile);
+        sh = flow_short(k.tile);
+        break;
+    case FAM_SMALL:
+        threads = 512;
+        stages = 1;
+        break;
+    case FAM_WAVE:
+        threads = wave_threads(k.tile);
+        stages = 4;
+        break;
+    case FAM_HALO:
+        threads = k.tile * 64;
+        stages = 1;
+        break;
+    case FAM_WIN: threads = win_threads(k.tile); break;
+    default: threads = tap_threads(k.tile); break;
+    }
+    char buf[120];
+    snprintf(buf, sizeof buf, "%s tile=%dx%dx%d threads=%d stages=%d%s", fam_name[k.fam], ts.tc, ts.tp, ts.bk, threads,
+             stages, sh ? "s" : "");
+    return buf;
+}
+
 // Tiling of the launched kernel: tile counts, K-steps, persistent grid.
 // The padding correction tables (pcorr_tab, pcls_tab) belong to the
 // LDS-direct kernel only: the other families gather zp_x themselves.
@@ -729,6 +770,10 @@ std::string tune_key(const ConvDesc &d, bool term3, size_t ncls, bool fast)
              (int)fast, d.y_ldc, d.y_coff);
     return buf;
 }
+
+// Key suffix of the kernel that takes over when a residual add is fused into a
+// plan whose own kernel has no such form (recorded beside its own).
+const char kWithAdd[] = "+add";
 
 bool tune_lookup(const std::string &key, const std::vector<ConvKernel> &cands, ConvKernel *out)
 {
@@ -1380,12 +1425,20 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
             p->fuse_ker = default_kernel(fusable, M, d.K, (int)((Jf + 63) / 64));
         if (M > 0 && env_int("QNN_AUTOTUNE", 1) != 0)
             tune_now = !tune_lookup(key, cands, &best) && tune;
+        // a choice without a fused add was recorded with the fastest that has one
+        ConvKernel with_add;
+        if (!tune_now && best.fam == FAM_FLOW && !can_fuse(best) && tune_lookup(key + kWithAdd, timed, &with_add) &&
+            can_fuse(with_add))
+            p->fuse_ker = with_add;
     }
 
     // ---- device tables: those that the kernels to be timed, or the chosen
     // one, read and no others (a one-shot call pays for all of it each time)
+    std::vector<ConvKernel> read = tune_now ? timed : std::vector<ConvKernel>{best};
+    if (best.fam == FAM_FLOW && !can_fuse(best) && can_fuse(p->fuse_ker))
+        read.push_back(p->fuse_ker);
     auto uses = [&](std::initializer_list<int> fams) {
-        for (const ConvKernel &k : tune_now ? timed : std::vector<ConvKernel>{best})
+        for (const ConvKernel &k : read)
             if (std::find(fams.begin(), fams.end(), k.fam) != fams.end())
                 return true;
         return false;
@@ -1487,6 +1540,8 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
             return s;
         }
         tune_record(key, best);
+        if (best.fam == FAM_FLOW && !can_fuse(best) && can_fuse(p->fuse_ker))
+            tune_record(key + kWithAdd, p->fuse_ker);
     }
     p->ker = best;
     set_tiling(a, best, p->avec, pcorr_tab, pcls_tab);
@@ -1500,35 +1555,18 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
         p->ws_part_bytes = (size_t)a.ntiles * a.ksplit * st_.tc * st_.tp * sizeof(int32_t);
         p->ws_bytes += p->ws_cnt_bytes + p->ws_part_bytes;
     }
-    const TileShape ts = kernel_shape(best);
-    static const char *fam_name[] = {"conv_mfma", "conv_tap",    "conv_dma",     "conv_wave",
-                                     "conv_halo", "conv_window", "conv_dma_flow", "conv_dma_small"};
     char buf[200];
-    if (best.fam == FAM_GATHER)
+    if (best.fam == FAM_GATHER) {
+        const TileShape ts = kernel_shape(best);
         snprintf(buf, sizeof buf,
                  "conv_mfma tile=%dx%dx%d gather=%d tiles=%d grid=%d term3=%d cpad=%d M=%lld K=%d J=%lld cands=%d",
                  ts.tc, ts.tp, ts.bk, p->avec, a.ntiles, a.nblocks, (int)term3, C4 != d.C, (long long)M, d.K,
                  (long long)Jg, (int)cands.size());
-    else
-        snprintf(buf, sizeof buf,
-                 "%s tile=%dx%dx%d threads=%d stages=%d%s tiles=%d term3=%d border=%d M=%lld K=%d J=%lld cands=%d",
-                 fam_name[best.fam], ts.tc, ts.tp, ts.bk,
-                 best.fam == FAM_DMA    ? dma_threads(best.tile)
-                 : best.fam == FAM_FLOW ? flow_threads(best.tile)
-                 : best.fam == FAM_SMALL ? 512
-                 : best.fam == FAM_WAVE ? wave_threads(best.tile)
-                 : best.fam == FAM_HALO ? best.tile * 64
-                 : best.fam == FAM_WIN  ? win_threads(best.tile)
-                                        : tap_threads(best.tile),
-                 best.fam == FAM_DMA    ? dma_stages(best.tile)
-                 : best.fam == FAM_FLOW ? flow_stages(best.tile)
-                 : best.fam == FAM_WAVE ? 4
-                 : best.fam == FAM_HALO || best.fam == FAM_SMALL ? 1
-                                                                 : 2,
-                 (best.fam == FAM_DMA && dma_short(best.tile)) || (best.fam == FAM_FLOW && flow_short(best.tile)) ? "s"
-                                                                                                                : "",
-                 a.ntiles, (int)term3,
-                 (int)ncls, (long long)M, d.K, (long long)Jg, (int)cands.size());
+    } else {
+        snprintf(buf, sizeof buf, "%s tiles=%d term3=%d border=%d M=%lld K=%d J=%lld cands=%d",
+                 kernel_text(best).c_str(), a.ntiles, (int)term3, (int)ncls, (long long)M, d.K, (long long)Jg,
+                 (int)cands.size());
+    }
     if (best.fam == FAM_WAVE) {
         const size_t n = strlen(buf);
         snprintf(buf + n, sizeof buf - n, " split=%d", best.tile);
@@ -2237,11 +2275,8 @@ qnn_status qnn_plan_set_residual(qnn_plan *plan, qnn_dtype r_dtype, qnn_qparams 
     if (ker.fam != plan->ker.fam || ker.tile != plan->ker.tile) {
         plan->ker = ker;
         set_tiling(plan->conv, ker, plan->avec, nullptr, nullptr);   // no padding corrections (1x1 filters)
-        const TileShape ts = kernel_shape(ker);
-        char buf[120];
-        snprintf(buf, sizeof buf, "conv_dma_flow tile=%dx%dx%d threads=%d stages=%d%s tiles=%d", ts.tc, ts.tp, ts.bk,
-                 flow_threads(ker.tile), flow_stages(ker.tile), flow_short(ker.tile) ? "s" : "", plan->conv.ntiles);
-        plan->desc = buf + plan->desc.substr(plan->desc.find(" term3="));
+        plan->desc = kernel_text(ker) + " tiles=" + std::to_string(plan->conv.ntiles) +
+                     plan->desc.substr(plan->desc.find(" term3="));
     }
     plan->conv.fadd = args;
     plan->conv.r_ldc = r_ldc;

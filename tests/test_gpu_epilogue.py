@@ -89,6 +89,46 @@ def test_largest_tile_gives_way(tmp_path):
     assert_equal(y, O.add(mid, c.s_y, c.zp_y, r, 0.03, 7, 0.05, 9, "u8"), "fused after giving way")
 
 
+@pytest.mark.parametrize("choice,prefix", [("6 4 1", "conv_dma_flow tile=256x128x64 threads=512 stages=4 tiles=16 "),
+                                           ("6 16 1", "conv_dma_flow tile=64x64x64 threads=256 stages=4s tiles=128 "),
+                                           ("7 5 1", "conv_dma_small tile=32x64x64 threads=512 stages=1 tiles=256 ")])
+def test_largest_tile_gives_way_as_recorded(choice, prefix, tmp_path):
+    """The kernel that takes over is recorded beside the choice."""
+    c = W.conv_case(L("g", 16, 16, 256, 512, 1, 1), 4, seed=2)
+    path = tmp_path / "choices.txt"
+    try:
+        Q.set_tuning_file(str(path))
+        p, keep = make_plan(c)
+        p.close()
+        key = path.read_text().split()[0]
+        path.write_text(f"{key} 6 6 1\n{key}+add {choice}\n")
+        Q.set_tuning_file(str(path))
+        p, keep = make_plan(c)
+    finally:
+        Q.set_tuning_file(None)
+    mid = run_oracle(c)
+    r = np.random.default_rng(1).integers(0, 256, size=mid.shape, dtype=np.int64).astype(np.uint8)
+    p.set_residual("u8", 0.03, 7, 0.05, 9, "u8")
+    assert p.describe().startswith(prefix), p.describe()
+    y = p.run(dev(c.x), residual=dev(r)).cpu().numpy()
+    p.close()
+    assert_equal(y, O.add(mid, c.s_y, c.zp_y, r, 0.03, 7, 0.05, 9, "u8"), "fused after giving way")
+
+
+def test_second_plan_gives_way_alike():
+    """A plan created from the choice that timing an equal one left behind."""
+    w = dev(np.random.default_rng(0).integers(-90, 91, size=(4096, 1, 1, 4096)).astype(np.int8))
+    seen = []
+    for _ in range(2):
+        p = Q.conv2d_plan((1, 64, 64, 4096), "u8", 0.02, 100, w, 0.01, 0, None, 1, 0, 1, 2.0, 3, "i8")
+        own = p.describe()
+        p.set_residual("i8", 0.03, 7, 0.05, 9, "i8")
+        seen.append((own, p.describe()))
+        p.close()
+    print(seen, flush=True)
+    assert seen[0] == seen[1], seen
+
+
 @pytest.mark.parametrize("knob", [dict(QNN_FLOW=0), dict(QNN_FLOW=3), dict(QNN_SMALL=0), dict(QNN_TILE=0)],
                          ids=lambda d: "".join(f"{k[4:].lower()}{v}" for k, v in d.items()))
 @pytest.mark.parametrize("R", [1, 3])
