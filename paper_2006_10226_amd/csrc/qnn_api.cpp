@@ -1423,8 +1423,12 @@ qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, boo
                 fusable.push_back(k);
         if (!fusable.empty())
             p->fuse_ker = default_kernel(fusable, M, d.K, (int)((Jf + 63) / 64));
+        // (files from before layers of these channel counts had border classes
+        // name them without)
         if (M > 0 && env_int("QNN_AUTOTUNE", 1) != 0)
-            tune_now = !tune_lookup(key, cands, &best) && tune;
+            tune_now = !(tune_lookup(key, cands, &best) ||
+                         (!tap_ok && ncls && tune_lookup(tune_key(d, term3, 0, fast), cands, &best))) &&
+                       tune;
         // a choice without a fused add was recorded with the fastest that has one
         ConvKernel with_add;
         if (!tune_now && best.fam == FAM_FLOW && !can_fuse(best) && tune_lookup(key + kWithAdd, timed, &with_add) &&

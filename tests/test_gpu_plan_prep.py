@@ -84,6 +84,30 @@ def test_recorded_family(i, tmp_path):
         Q.set_tuning_file(None)
 
 
+def test_recorded_without_border_classes(tmp_path):
+    """Files written when padded layers of such channel counts had no border
+    classes name them with none."""
+    c = W.conv_case(L("old", 12, 14, 48, 64, 3, 3, 1, (1, 1, 1, 1)), 2, seed=5)
+    path = tmp_path / "choices.txt"
+    try:
+        Q.set_tuning_file(str(path))
+        p, keep = make_plan(c)
+        p.close()
+        key = path.read_text().split()[0]
+        assert ":b9:" in key, key
+        path.write_text(key.replace(":b9:", ":b0:") + " 0 3 1\n")
+        Q.set_tuning_file(str(path))
+        p, keep = make_plan(c)
+        d = p.describe()
+        assert d.startswith("conv_mfma tile=64x64x128"), d
+        y = p.run(dev(c.x)).cpu().numpy()
+        p.close()
+        assert_equal(y, run_oracle(c), "recorded without classes")
+        assert len(path.read_text().split("\n")) == 2   # nothing timed anew
+    finally:
+        Q.set_tuning_file(None)
+
+
 def test_padding_adds_little_to_creation():
     """Without timing of candidates, as a one-shot call prepares. Padding took
     7 times the unpadded layer's time while each pixel's class was worked out
