@@ -11,7 +11,12 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 namespace conv {
 
-constexpr int kBufFlags = 0x00020000;   // raw buffer, 32-bit data format
+// Raw buffer, 32-bit data format. Its range check, as measured on gfx950 for
+// loads into registers and into LDS: a dword whose vector plus scalar offset
+// is at or past the descriptor's size, whatever the share of either (and also
+// at size 0), reads as zero and touches no memory; the dwords of one load are
+// checked one by one.
+constexpr int kBufFlags = 0x00020000;
 constexpr int kOutOfRange = (int)0x80000000;
 
 // Physical 16-byte chunk of logical chunk q in an LDS row of CPR chunks; it

@@ -20,14 +20,16 @@
 //     that is a multiple of 16 (per tap, after packing) streams at full rate;
 //   * a stage past the end of the reduction has its descriptor's size set to
 //     0 (LINEAR, weights) or an entry no pixel matches (TAB): the loads count
-//     but touch no memory.
+//     but touch no memory (the range check takes the scalar offset into
+//     account, see kBufFlags).
 // A step of a 64 x 64 tile is 19 instructions in LINEAR form and 27 in TAB
 // form. Measured (hot): dense 4096^3 79 -> 58 us (256 x 256 tile), 1x1 1024 ->
 // 256 at 14x14 batch 32 7.2 -> 5.7 us, 5x5 48 -> 64 at 35x35 batch 64 22.4 ->
 // 12.0 us and 3x3 96 -> 96 28.5 -> 17.7 us (both from the gather kernel).
 // Bytes of a chunk that lie past its pixel's channels (a channel count that
 // is not a multiple of 64 in LINEAR form, of 16 in TAB form) are the next
-// pixel's, or zeros past the end of x, and meet zero weights.
+// pixel's, or zeros past the end of x (the same range check), and meet zero
+// weights.
 #pragma once
 
 #include "conv_dma_kernel.h"

@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(kSmallWaves * 64, 2) conv_small_kernel(ConvArg
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int ks = __builtin_amdgcn_readfirstlane(kstep(i0 + u));
-            const bool live = ks < nk;   // steps past the end read zeros and touch no memory
+            const bool live = ks < nk;   // steps past the end: size 0, zeros, no memory touched (kBufFlags)
             const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)a.wf, (short)0, live ? a.Kpad * a.fJpad : 0, kBufFlags);
             const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(

@@ -110,3 +110,24 @@ def test_dense_largest_tile_grouped(M, K, N):
         c = W.dense_case(W.DenseLayer("d", m, k, n), seed=M)
         with env(QNN_FLOW=tile):
             assert_equal(run_gpu(c), run_oracle(c), f"dense {m} {k} {n} flow {tile}")
+
+
+@pytest.mark.parametrize("layer,knobs", [
+    # weights beyond 4 MB: the channel tiles of four pixel tiles in turn, the last group of fewer
+    (L("il", 9, 37, 4100, 1100, 1, 1), [dict(QNN_FLOW=t) for t in (0, 3, 4, 6, 9, 19)]),
+    # 900 K-steps: a chunk table of 29 KB; 938 without one
+    (L("15x15", 8, 8, 256, 32, 15, 15, 1, (7, 7, 7, 7)), [dict(QNN_FLOW=0), dict(QNN_FLOW=4), dict(QNN_SMALL=0)]),
+    (L("long", 2, 3, 60000, 48, 1, 1), [dict(QNN_FLOW=0), dict(QNN_FLOW=7), dict(QNN_SMALL=3)]),
+], ids=lambda v: getattr(v, "name", None))
+def test_large_weights_and_long_reductions(layer, knobs):
+    c = W.conv_case(layer, 1, seed=5)
+    ref = run_oracle(c)
+    for knob in knobs:
+        with env(**knob):
+            p, keep = make_plan(c)
+        d = p.describe()
+        y = p.run(dev(c.x)).cpu().numpy()
+        p.close()
+        print(layer.name, knob, d, flush=True)
+        assert "cands=1" in d.split() and d.startswith("conv_dma_flow" if "QNN_FLOW" in knob else "conv_dma_small"), d
+        assert_equal(y, ref, f"{layer.name} {knob}: {d}")
