@@ -447,13 +447,15 @@ size_t qnn_plan_workspace_size(const qnn_plan *plan);
 const char *qnn_plan_describe(const qnn_plan *plan);
 
 /*
- * Kernel-choice file.  A conv or dense plan picks its kernel by timing the
- * eligible candidate kernels on its own shape at creation (each candidate
- * computes the same bytes; only the time differs).  After this call with a
+ * Kernel-choice file.  A conv or dense plan picks its kernel by timing
+ * candidate kernels on its own shape at creation (each candidate computes the
+ * same bytes; only the time differs).  After this call with a
  * path, creation first looks its shape up in the file's records and, when
- * the recorded choice is still a candidate, takes it without timing; a
- * choice it does time is appended to the file as one text line,
- * "<shape key> <family> <config>".  A missing file starts empty.  NULL or
+ * the recorded choice is a candidate (whether or not it would be timed
+ * today), takes it without timing; a choice it does time is appended to the
+ * file as one text line, "<shape key> <family> <config> <split>", followed,
+ * where its kernel has no fused add, by one more with "+add" after the key
+ * for the kernel that qnn_plan_set_residual turns to.  A missing file starts empty.  NULL or
  * "" stops reading and writing any file and forgets the records.  Returns
  * QNN_ERR_UNSUPPORTED when the file exists but cannot be read.  Plans
  * created concurrently with this call see either the old or the new

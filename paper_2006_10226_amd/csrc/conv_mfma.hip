@@ -556,7 +556,8 @@ __global__ void __launch_bounds__(256) pad_channels_kernel(const uint8_t *x, uin
 // Bound by reading x once; one thread per pixel reading byte by byte took
 // 135 us for a 64 x 17 x 17 x 160 input and a 1x7 window (3 MB; 1136-byte
 // strides between lanes, R*S passes over x), and takes about 4 us now: the
-// whole call, with its conv, went from 152 to 22.9 us.  A pixel's channels are
+// whole call, with its conv, went from 152 to 22.9 us (19 us with the conv
+// kernels of today).  A pixel's channels are
 // split over `lanes` neighbouring lanes (16-byte loads where the pixels are
 // 16-byte aligned, else 4), four bytes summed per v_dot4, and the lanes'
 // sums meet in a butterfly.

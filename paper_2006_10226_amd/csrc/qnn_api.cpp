@@ -893,9 +893,6 @@ int device_cus()
     return cus;
 }
 
-// tune: time the candidate kernels when the kernel-choice records hold no
-// choice for this shape (plans); one-shot calls pass false and take the
-// recorded choice or else the first candidate, without timing.
 // ---- depthwise 3x3 kernel configurations
 // A choice is kept as a ConvKernel: fam 0 = register kernel (tile = strips
 // per work item), fam 1 = band kernel (tile = rows | strips << 8, split =
@@ -1043,6 +1040,10 @@ qnn_status autotune_dw(const DwArgs &base, const std::vector<ConvKernel> &cands,
     return s;
 }
 
+// tune: time the candidate kernels when the kernel-choice records hold no
+// choice for this shape (plans); one-shot calls pass false and take the
+// recorded choice or else default_kernel's (depthwise, and where only older
+// families apply: the first candidate), without timing.
 qnn_status make_conv_plan(const ConvDesc &d, hipStream_t st, qnn_plan **out, bool tune = true)
 {
     int32_t Ho, Wo, lo, hi;
