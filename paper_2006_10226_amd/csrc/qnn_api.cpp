@@ -478,7 +478,9 @@ void add_flow_candidates(std::vector<ConvKernel> &c, int64_t M, int K, int nk, b
 // (one-shot calls): the largest few-pixel tile that still makes three
 // workgroups for every four CUs where 64 x 64 tiles would leave CUs idle; else
 // a short form for up to four K-steps, 128 x 128 tiles where they give every
-// CU two, 64 x 64 otherwise.
+// CU two (64 x 128 where those would compute a block of 64 channels that the
+// layer does not have: one-shot 5x5 48 -> 64 at 35x35 batch 64 108 -> 94 us),
+// 64 x 64 otherwise.
 ConvKernel default_kernel(const std::vector<ConvKernel> &c, int64_t M, int K, int nk)
 {
     auto has = [&](int fam, int tile) {
@@ -497,7 +499,9 @@ ConvKernel default_kernel(const std::vector<ConvKernel> &c, int64_t M, int K, in
     for (int t : {FLOW_64x64_R1, FLOW_64x64_R2, FLOW_64x64_R4})
         if (has(FAM_FLOW, t) && nk <= flow_stages(t))
             return {FAM_FLOW, t};
-    const int t = tiles(flow_tile_shape(FLOW_128x128)) >= 2 * cus ? FLOW_128x128 : FLOW_64x64;
+    int t = FLOW_64x64;
+    if (tiles(flow_tile_shape(FLOW_128x128)) >= 2 * cus)
+        t = (K + 63) / 64 % 2 ? FLOW_64x128 : FLOW_128x128;
     return has(FAM_FLOW, t) ? ConvKernel{FAM_FLOW, t} : c[0];
 }
 

@@ -108,6 +108,20 @@ def test_recorded_without_border_classes(tmp_path):
         Q.set_tuning_file(None)
 
 
+@pytest.mark.parametrize("cout,tile", [(32, "64x128x64"), (64, "64x128x64"), (100, "128x128x64"), (130, "64x128x64")])
+def test_untimed_tile_fits_the_channels(cout, tile):
+    """What a one-shot call takes where 128 x 128 tiles fill the chip: no block
+    of 64 channels that the layer does not have."""
+    c = W.conv_case(L("u", 92, 93, 32, cout, 3, 3, 1, (1, 1, 1, 1)), 8, seed=cout)
+    with env(QNN_AUTOTUNE=0):
+        p, keep = make_plan(c)
+    d = p.describe()
+    y = p.run(dev(c.x)).cpu().numpy()
+    p.close()
+    assert d.startswith(f"conv_dma_flow tile={tile} "), d
+    assert_equal(y, run_oracle(c), d)
+
+
 def test_padding_adds_little_to_creation():
     """Without timing of candidates, as a one-shot call prepares. Padding took
     7 times the unpadded layer's time while each pixel's class was worked out
